@@ -87,16 +87,19 @@ struct Layout {
 
 #define SLOT_END() __builtin_amdgcn_sched_barrier(0)
 
-// RAGGED: some tile reaches past L, C or R (copies check every lane and read
-// the zero page outside the tensors); otherwise copies use uniform bases plus
-// fixed per-lane offsets.
+// Copies as in the forward: token rows past L and columns past C are not
+// read (their lanes copy the last row or column chunk that exists, and what
+// they lead to is never stored), so any L and C take the copies of a uniform
+// base plus fixed offsets.  KRAG: the last K-step reaches past R, or the
+// offsets exceed 32 bits; every copy then checks its lanes and reads the zero
+// page outside the tensors.
 // PASS2: the second pass of a rank above 64 (ranks 64.. of B and A): W is
 // taken as zero and the product is added onto dX.  ldb: row stride of B.
 // r: the rank the kernel works on, a multiple of 8 (B's columns ra .. r-1
 // are zero); ra: the rows of A that exist (A rows ra .. r-1 are read as zero).
-// TM, NF < (BM, 2): a thin tile of TM tokens and 128 NF input features
-// (whole-tile shapes, one pass), as in the forward kernel.
-template <int RK, bool RAGGED, bool PASS2, bool FOLD, int TM, int NF>
+// TM, NF < (BM, 2): a thin tile of TM tokens and 128 NF input features (one
+// pass), as in the forward kernel.
+template <int RK, bool KRAG, bool PASS2, bool FOLD, int TM, int NF>
 __global__ __launch_bounds__(NT, 1) void dx_kernel(
     const uint16_t* __restrict__ dY, const uint16_t* __restrict__ W,
     const uint32_t* __restrict__ Mt, const uint16_t* __restrict__ Bm,
@@ -105,7 +108,7 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
     float* __restrict__ z1, int64_t nz1, int n_full, int split, float* __restrict__ part) {
     using Lay = Layout<RK, TM, NF>;
     constexpr int MBW = TM / 32;  // 32-token blocks per wave
-    static_assert((TM == BM && NF == 2) || (!RAGGED && !PASS2), "thin tiles: fixed-offset copies, one pass");
+    static_assert((TM == BM && NF == 2) || !PASS2, "thin tiles: one pass");
     static_assert(Lay::TOTAL <= 160 * 1024, "LDS budget");
     static_assert(4 * TM * 64 * NF <= 2 * Lay::STAGE, "output staging fits the stage buffers");
     // the prologue parks the merge's A block in stage 1: in its dY region,
@@ -151,7 +154,11 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
         nk = (R + BK - 1) / BK;
         m0 = (int64_t)tm * BM + (int64_t)(u % (BM / TM)) * TM;
         n0 = tn * BN + (u / (BM / TM)) * Lay::FT;
+        if (m0 >= L || n0 >= C) return;  // a part of an edge tile that holds no output
     }
+    // last row of the dY slab, last column chunk and last column that exist
+    const int lastm = (int)min(L - 1 - m0, (int64_t)(TM - 1));
+    const int lastc = C - 8 - n0, lastn = C - 1 - n0;
     const int kofs = kbeg * BK;
     const int wprT = (R + 31) >> 5;  // words per row of M^T
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
@@ -185,16 +192,16 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
 #pragma unroll
     for (int q = 0; q < Lay::ND; ++q) {
         const int rd = 8 * (Lay::ND * wave + q) + (lane >> 3);
-        offD[q] = (uint32_t)((rd * R + 8 * ((lane & 7) ^ ((rd >> 1) & 7))) * 2);
+        offD[q] = (uint32_t)((min(rd, lastm) * R + 8 * ((lane & 7) ^ ((rd >> 1) & 7))) * 2);
     }
 #pragma unroll
     for (int q = 0; q < Lay::NWC; ++q) {
         if constexpr (NF == 2) {
             const int rw = 8 * q + (lane >> 3);
-            offW[q] = (uint32_t)((rw * C + 64 * wave + 8 * ((lane & 7) ^ tr64_swz(rw))) * 2);
+            offW[q] = (uint32_t)((rw * C + min(64 * wave + 8 * ((lane & 7) ^ tr64_swz(rw)), lastc)) * 2);
         } else {
             const int rw = 16 * q + (lane >> 2);
-            offW[q] = (uint32_t)((rw * C + 32 * wave + 8 * (lane & 3)) * 2);
+            offW[q] = (uint32_t)((rw * C + min(32 * wave + 8 * (lane & 3), lastc)) * 2);
         }
     }
     // M^T words of a K-step: with whole tiles the tile's columns hold them
@@ -202,7 +209,10 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
     // of a wave moves 256 consecutive bytes of it
     uint32_t offM[Lay::NMC];
 #pragma unroll
-    for (int q = 0; q < Lay::NMC; ++q) offM[q] = (uint32_t)((64 * (Lay::NMC * wave + q) + lane) * 4);
+    for (int q = 0; q < Lay::NMC; ++q) {
+        const int e = 64 * (Lay::NMC * wave + q) + lane;
+        offM[q] = (uint32_t)((2 * min(e >> 1, lastn) + (e & 1)) * 4);
+    }
     const uint16_t* Dt = uniform_ptr(dY + m0 * R);
     const uint16_t* Wn = uniform_ptr(W + n0);
     const uint32_t* Mn = uniform_ptr(Mt + 2 * (int64_t)n0);
@@ -212,7 +222,7 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
         if (j < Lay::ND) {
             const int q = j, blk = Lay::ND * wave + q;
             const uint32_t dst = sb + Lay::D + 1024 * blk;
-            if constexpr (!RAGGED) {
+            if constexpr (!KRAG) {
                 copy16s_to_lds(uniform_ptr(Dt + k0), offD[q], dst);
             } else {
                 const int row = 8 * blk + (lane >> 3);
@@ -224,11 +234,11 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
             if (PASS2) return;  // W is zero: its slabs were cleared once
             const int q = j - Lay::ND;
             const uint32_t dst = sb + Lay::W + Lay::WBW * wave + 1024 * q;
-            if constexpr (!RAGGED) {
+            if constexpr (!KRAG) {
                 copy16s_to_lds(uniform_ptr(Wn + (int64_t)k0 * C), offW[q], dst);
             } else {
-                const int row = 8 * q + (lane >> 3);
-                const int col = 64 * wave + 8 * ((lane & 7) ^ tr64_swz(row));
+                const int row = NF == 2 ? 8 * q + (lane >> 3) : 16 * q + (lane >> 2);
+                const int col = NF == 2 ? 64 * wave + 8 * ((lane & 7) ^ tr64_swz(row)) : 32 * wave + 8 * (lane & 3);
                 const bool ok = k0 + row < R && n0 + col < C;
                 copy16_to_lds(ok ? (const void*)(Wn + (int64_t)(k0 + row) * C + col) : (const void*)zsrc, dst);
             }
@@ -237,13 +247,13 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
             // copies, those past the slab go to the sink
             const int q = j - Lay::ND - Lay::NWC, blk = 4 * q + wave;
             const bool real = blk < Lay::NBC;
-            const bool ok = bval[q] && (!RAGGED || k0 + brow[q] < R);
+            const bool ok = bval[q] && (!KRAG || k0 + brow[q] < R);
             const void* src = (const uint8_t*)Bm + ((int64_t)k0 + brow[q]) * (2 * (int64_t)ldb) + bcol[q];
             copy16_to_lds(ok ? src : (const void*)zsrc, real ? sb + Lay::B + 1024 * blk : lds0 + Lay::SINK);
         } else {
             const int q = j - Lay::ND - Lay::NWC - Lay::NB;
             const uint32_t dst = sb + Lay::M + 256 * (Lay::NMC * wave + q);
-            if constexpr (!RAGGED) {
+            if constexpr (!KRAG) {
                 copy4s_to_lds(uniform_ptr(Mn + (int64_t)(k0 >> 5) * C), offM[q], dst);
             } else {
                 const int e = 64 * (Lay::NMC * wave + q) + lane;
@@ -593,10 +603,10 @@ bool power_of_two(float s) {
 }
 
 // z0, z1: dB (R x rank) and dA (rank x C) to clear, or null
-template <int RK, bool RAGGED, bool PASS2, bool FOLD, int TM, int NF>
+template <int RK, bool KRAG, bool PASS2, bool FOLD, int TM, int NF>
 void launch_tm(const LayerArgs& a, hipStream_t st, int ldb, int ra, int grid, int tiles_m, int tiles_n, int n_full,
                int split, float* part, float* z0, int64_t nz0, float* z1, int64_t nz1) {
-    hipLaunchKernelGGL((dx_kernel<RK, RAGGED, PASS2, FOLD, TM, NF>), dim3(grid), dim3(NT), 0, st, (const uint16_t*)a.dY,
+    hipLaunchKernelGGL((dx_kernel<RK, KRAG, PASS2, FOLD, TM, NF>), dim3(grid), dim3(NT), 0, st, (const uint16_t*)a.dY,
                        (const uint16_t*)a.W, a.Mt, (const uint16_t*)a.B, (const uint16_t*)a.A, (uint16_t*)a.dX, a.L,
                        (int)a.R, (int)a.C, (int)a.r, ra, a.scale, tiles_m, tiles_n, ldb, z0, nz0, z1, nz1, n_full,
                        split, part);
@@ -609,17 +619,16 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st, int ldb, int ra, bool c
     const int tiles_m = (int)((a.L + BM - 1) / BM);
     const int tiles_n = (int)((a.C + BN - 1) / BN);
     const int tiles = tiles_m * tiles_n;
-    // fixed-offset copies: whole tiles and K-steps, and per-lane byte
-    // offsets (256 dY rows of R, 64 W rows of C, 256 M^T rows) inside 32 bits
-    const bool ragged = !dx_whole_tiles(a.L, a.R, a.C);
-    const bool fold = !ragged && power_of_two(a.scale);  // whole tiles with a power-of-two scale
-    // A short last wave on a whole-tile shape runs as thin tiles (the same
-    // bits, no workspace); on other shapes it is cut over K when the caller
-    // gave room for the pieces' partial sums (one pass only: ranks up to 64).
-    const ThinPlan tp = (!ragged && !PASS2) ? thin_plan(tiles) : ThinPlan{tiles, 0, 1};
+    const bool krag = !dx_fixed_copies(a.R, a.C);
+    const bool fold = !krag && power_of_two(a.scale);  // fixed-offset copies with a power-of-two scale
+    // A short last wave is cut over K when the caller gave room for the
+    // pieces' partial sums (shapes without whole tiles, one pass only: ranks
+    // up to 64); otherwise it runs as thin tiles (the same bits as whole
+    // ones, no workspace).
     TailSplit sp{tiles, 1, tiles};
-    if (tp.q == 1 && a.split_ws != nullptr && !PASS2 && ldb <= 64)
+    if (a.split_ws != nullptr && !PASS2 && ldb <= 64 && !dx_whole_tiles(a.L, a.R, a.C))
         sp = tail_split(tiles, (a.R + BK - 1) / BK, a.split_budget);
+    const ThinPlan tp = (sp.split == 1 && !PASS2) ? thin_plan(tiles) : ThinPlan{tiles, 0, 1};
     float* part = sp.split > 1 ? (float*)a.split_ws : nullptr;
     // with thin tiles the whole-tile grid is exactly the first n_full tiles
     // (work_coords regroups ids over the tiles it is told the grid holds)
@@ -632,7 +641,7 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st, int ldb, int ra, bool c
     float* z1 = clear_here ? a.dA : nullptr;
     const int64_t nz0 = clear_here ? a.R * a.r_grad : 0, nz1 = clear_here ? a.r_grad * a.C : 0;
     if (grid > 0) {
-        if (ragged)
+        if (krag)
             launch_tm<RK, true, PASS2, false, BM, 2>(a, st, ldb, ra, grid, tiles_m, tiles_n, n_full, sp.split, part, z0,
                                                   nz0, z1, nz1);
         else if (fold)
@@ -667,25 +676,25 @@ hipError_t launch_ranks(const LayerArgs& a, hipStream_t st, bool pass2, int ldb,
 #else  // LORS_THIN_TILES
 
 // thin tiles of one feature half (NF = 1) and TM tokens: 2 BM / TM per tile
-template <int RK, bool FOLD, int TM>
+template <int RK, bool KRAG, bool FOLD, int TM>
 hipError_t launch_thin_tm(const LayerArgs& a, hipStream_t st, int ldb, int ra, int first, int tail, bool clear) {
     const int tiles_m = (int)((a.L + BM - 1) / BM);
     const int tiles_n = (int)((a.C + BN - 1) / BN);
     float* z0 = clear ? a.dB : nullptr;
     float* z1 = clear ? a.dA : nullptr;
     const int64_t nz0 = clear ? a.R * a.r_grad : 0, nz1 = clear ? a.r_grad * a.C : 0;
-    launch_tm<RK, false, false, FOLD, TM, 1>(a, st, ldb, ra, tail * (2 * BM / TM), tiles_m, tiles_n, first, tail, nullptr,
+    launch_tm<RK, KRAG, false, FOLD, TM, 1>(a, st, ldb, ra, tail * (2 * BM / TM), tiles_m, tiles_n, first, tail, nullptr,
                                           z0, nz0, z1, nz1);
     return hipGetLastError();
 }
 
-template <int RK, bool FOLD>
+template <int RK, bool KRAG, bool FOLD>
 hipError_t launch_thin_q(const LayerArgs& a, hipStream_t st, int ldb, int ra, int first, int tail, int q,
                          bool clear) {
     switch (q) {  // q thin tiles per tile: two feature halves, each cut into q/2 token parts
-        case 2: return launch_thin_tm<RK, FOLD, BM>(a, st, ldb, ra, first, tail, clear);
-        case 4: return launch_thin_tm<RK, FOLD, BM / 2>(a, st, ldb, ra, first, tail, clear);
-        case 8: return launch_thin_tm<RK, FOLD, BM / 4>(a, st, ldb, ra, first, tail, clear);
+        case 2: return launch_thin_tm<RK, KRAG, FOLD, BM>(a, st, ldb, ra, first, tail, clear);
+        case 4: return launch_thin_tm<RK, KRAG, FOLD, BM / 2>(a, st, ldb, ra, first, tail, clear);
+        case 8: return launch_thin_tm<RK, KRAG, FOLD, BM / 4>(a, st, ldb, ra, first, tail, clear);
         default: return hipErrorInvalidValue;
     }
 }
@@ -693,8 +702,9 @@ hipError_t launch_thin_q(const LayerArgs& a, hipStream_t st, int ldb, int ra, in
 template <int RK>
 hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int ldb, int ra, int first, int tail, int q,
                           bool clear) {
-    return power_of_two(a.scale) ? launch_thin_q<RK, true>(a, st, ldb, ra, first, tail, q, clear)
-                                 : launch_thin_q<RK, false>(a, st, ldb, ra, first, tail, q, clear);
+    if (!dx_fixed_copies(a.R, a.C)) return launch_thin_q<RK, true, false>(a, st, ldb, ra, first, tail, q, clear);
+    return power_of_two(a.scale) ? launch_thin_q<RK, false, true>(a, st, ldb, ra, first, tail, q, clear)
+                                 : launch_thin_q<RK, false, false>(a, st, ldb, ra, first, tail, q, clear);
 }
 
 #endif  // LORS_THIN_TILES
@@ -707,7 +717,7 @@ hipError_t launch_dx_thin_bf16(const LayerArgs& a, hipStream_t st, int ldb, int 
                                bool clear) {
     if (tail <= 0) return hipSuccess;
     // a.r: this pass's rank, a multiple of 8 up to 64 (see launch_dx_bf16)
-    if (!dx_whole_tiles(a.L, a.R, a.C) || a.r < 8 || a.r > 64 || a.r % 8 != 0) return hipErrorInvalidValue;
+    if (a.r < 8 || a.r > 64 || a.r % 8 != 0) return hipErrorInvalidValue;
     switch ((a.r + 15) / 16) {
         case 1: return launch_thin_rk<1>(a, st, ldb, ra, first, tail, q, clear);
         case 2: return launch_thin_rk<2>(a, st, ldb, ra, first, tail, q, clear);

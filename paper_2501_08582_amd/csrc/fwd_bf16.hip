@@ -88,17 +88,20 @@ struct Layout {
 // 4-row fragments (the X/W slabs' row-pair XOR would leave those reads 2-way
 // conflicted).
 
-// RAGGED: some tile reaches past L, R or C (copies then check every lane and
-// read the zero page outside the tensors); otherwise every slab row and
-// K-chunk is in range and copies use a uniform base plus fixed offsets.
+// Copies.  Rows past L or R are not read: their lanes copy the last row that
+// exists instead (offsets fixed in the prologue), and the outputs they lead
+// to are never stored.  So any L and R take the copies of a uniform base plus
+// fixed offsets.  KRAG: the last K-step reaches past C, or the offsets exceed
+// 32 bits; every copy then checks its lanes and reads the zero page outside
+// the tensors.
 // PASS2: the second pass of a rank above 64 (ranks 64.. of B and A): W is
 // taken as zero and the product is added onto Y.  ldb: row stride of B.
 // TM, NF < (BM, 2): a thin tile of TM tokens and 128 NF features
-// (whole-tile shapes, one pass); each wave then holds TM x 32 NF
+// (one pass); each wave then holds TM x 32 NF
 // accumulators, merges 32 NF rows of W', and the MFMA slots, X reads and
 // merge pieces of the missing token and feature blocks drop out of the
 // schedule.
-template <int RK, bool TWO_FOUR, bool RAGGED, bool PASS2, bool FOLD, int TM, int NF>
+template <int RK, bool TWO_FOUR, bool KRAG, bool PASS2, bool FOLD, int TM, int NF>
 __global__ __launch_bounds__(NT, 1) void fwd_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
     const uint32_t* __restrict__ Mp, const uint16_t* __restrict__ Bm,
@@ -107,7 +110,7 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
     int tiles_n, int ldb, int n_full, int split, float* __restrict__ part) {
     using Lay = Layout<RK, TM, NF>;
     constexpr int MBW = TM / 32;  // 32-token blocks per wave
-    static_assert((TM == BM && NF == 2) || (!RAGGED && !PASS2), "thin tiles: fixed-offset copies, one pass");
+    static_assert((TM == BM && NF == 2) || !PASS2, "thin tiles: one pass");
     static_assert(Lay::TOTAL <= 160 * 1024, "LDS budget");
     static_assert(4 * TM * 64 * NF <= 2 * Lay::STAGE, "output staging fits the stage buffers");
     __shared__ __attribute__((aligned(1024))) uint8_t smem[Lay::TOTAL];
@@ -138,7 +141,11 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
         nk = (C + BK - 1) / BK;
         m0 = (int64_t)tm * BM + (int64_t)(u % (BM / TM)) * TM;
         n0 = tn * BN + (u / (BM / TM)) * Lay::FT;
+        if (m0 >= L || n0 >= R) return;  // a part of an edge tile that holds no output
     }
+    // last rows of the X and W slabs that exist
+    const int lastm = (int)min(L - 1 - m0, (int64_t)(TM - 1));
+    const int lastn = min(R - 1 - n0, Lay::FT - 1);
     const int kofs = kbeg * BK;
     const int wpr = (C + 31) >> 5;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
@@ -185,13 +192,13 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
     for (int q = 0; q < Lay::NX; ++q) {
         const int row = 8 * (Lay::NX * wave + q) + (lane >> 3);
         const int lc = (lane & 7) ^ ((row >> 1) & 7);
-        offX[q] = (uint32_t)((row * C + 8 * lc) * 2);
+        offX[q] = (uint32_t)((min(row, lastm) * C + 8 * lc) * 2);
     }
 #pragma unroll
     for (int q = 0; q < Lay::NWC; ++q) {
         const int row = 8 * (Lay::NWC * wave + q) + (lane >> 3);
         const int lc = (lane & 7) ^ ((row >> 1) & 7);
-        offW[q] = (uint32_t)((row * C + 8 * lc) * 2);
+        offW[q] = (uint32_t)((min(row, lastn) * C + 8 * lc) * 2);
     }
     // A slab: copy q of wave w is slab block 4q + w (rows 8 blk .. +7) when
     // that block exists; rows at or past r read zeros
@@ -207,7 +214,7 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
 #pragma unroll
     for (int q = 0; q < Lay::NMC; ++q) {
         const int e = 64 * (Lay::NMC * wave + q) + lane;
-        offM[q] = (uint32_t)(((e >> 1) * wpr + (e & 1)) * 4);
+        offM[q] = (uint32_t)((min(e >> 1, lastn) * wpr + (e & 1)) * 4);
     }
     const uint16_t* Xt = uniform_ptr(X + m0 * C);
     const uint16_t* Wt = uniform_ptr(W + (int64_t)n0 * C);
@@ -222,7 +229,7 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
             if (PASS2 && !isx) return;  // W is zero: its slabs were cleared once
             const int blk = isx ? Lay::NX * wave + q : Lay::NWC * wave + q;
             const uint32_t dst = sb + (isx ? Lay::X : Lay::W) + 1024 * blk;
-            if constexpr (!RAGGED) {
+            if constexpr (!KRAG) {
                 copy16s_to_lds(uniform_ptr((isx ? Xt : Wt) + k0), isx ? offX[q] : offW[q], dst);
             } else {
                 const int row = 8 * blk + (lane >> 3);
@@ -237,13 +244,13 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
             const bool has = blk < 2 * RK;
             const int row = 8 * blk + (lane >> 3);
             const int lc = (lane & 7) ^ tr64_swz(row);
-            const bool ok = has && row < r && (!RAGGED || k0 + 8 * lc < C);
+            const bool ok = has && row < r && (!KRAG || k0 + 8 * lc < C);
             copy16_to_lds(ok ? (const void*)(aptr[q] + k0) : (const void*)zsrc,
                           has ? sb + Lay::A + 1024 * blk : lds0 + Lay::SINK);
         } else {
             const int q = j - Lay::NX - Lay::NWC - Lay::NAW;
             const uint32_t dst = sb + Lay::M + 256 * (Lay::NMC * wave + q);
-            if constexpr (!RAGGED) {
+            if constexpr (!KRAG) {
                 copy4s_to_lds(uniform_ptr(Mt + (k0 >> 5)), offM[q], dst);
             } else {
                 const int e = 64 * (Lay::NMC * wave + q) + lane;
@@ -569,10 +576,10 @@ bool power_of_two(float s) {
 
 #ifndef LORS_THIN_TILES
 
-template <int RK, bool TWO_FOUR, bool RAGGED, bool PASS2, bool FOLD>
+template <int RK, bool TWO_FOUR, bool KRAG, bool PASS2, bool FOLD>
 void launch_whole(const LayerArgs& a, hipStream_t st, int ldb, int grid, int tiles_m, int tiles_n, int n_full,
                   int split, float* part) {
-    hipLaunchKernelGGL((fwd_kernel<RK, TWO_FOUR, RAGGED, PASS2, FOLD, BM, 2>), dim3(grid), dim3(NT), 0, st,
+    hipLaunchKernelGGL((fwd_kernel<RK, TWO_FOUR, KRAG, PASS2, FOLD, BM, 2>), dim3(grid), dim3(NT), 0, st,
                        (const uint16_t*)a.X, (const uint16_t*)a.W, a.M, (const uint16_t*)a.B,
                        (const uint16_t*)a.A, (const uint16_t*)a.bias, (uint16_t*)a.Y, a.L, (int)a.R, (int)a.C,
                        (int)a.r, a.scale, tiles_m, tiles_n, ldb, n_full, split, part);
@@ -583,25 +590,23 @@ hipError_t launch_fmt(const LayerArgs& a, hipStream_t st, int ldb) {
     const int tiles_m = (int)((a.L + BM - 1) / BM);
     const int tiles_n = (int)((a.R + BN - 1) / BN);
     const int tiles = tiles_m * tiles_n;
-    // the fixed-offset copies need every tile and K-step in range and the
-    // per-lane byte offsets (256 slab rows of C bf16 or of the mask) inside
-    // 32 bits
-    const bool ragged = !fwd_whole_tiles(a.L, a.R, a.C);
-    const bool fold = !ragged && power_of_two(a.scale);  // whole tiles with a power-of-two scale
-    // A short last wave on a whole-tile shape runs as thin tiles (the same
-    // bits, no workspace); on other shapes it is cut over K when the caller
-    // gave room for the pieces' partial sums (one pass only: ranks up to 64).
-    const ThinPlan tp = (!ragged && !PASS2) ? thin_plan(tiles) : ThinPlan{tiles, 0, 1};
+    const bool krag = !fwd_fixed_copies(a.C);
+    const bool fold = !krag && power_of_two(a.scale);  // fixed-offset copies with a power-of-two scale
+    // A short last wave is cut over K when the caller gave room for the
+    // pieces' partial sums (shapes without whole tiles, one pass only: ranks
+    // up to 64); otherwise it runs as thin tiles (the same bits as whole
+    // ones, no workspace).
     TailSplit sp{tiles, 1, tiles};
-    if (tp.q == 1 && a.split_ws != nullptr && !PASS2 && a.r <= 64)
+    if (a.split_ws != nullptr && !PASS2 && a.r <= 64 && !fwd_whole_tiles(a.L, a.R, a.C))
         sp = tail_split(tiles, (a.C + BK - 1) / BK, a.split_budget);
+    const ThinPlan tp = (sp.split == 1 && !PASS2) ? thin_plan(tiles) : ThinPlan{tiles, 0, 1};
     float* part = sp.split > 1 ? (float*)a.split_ws : nullptr;
     // with thin tiles the whole-tile grid is exactly the first n_full tiles
     // (work_coords regroups ids over the tiles it is told the grid holds)
     const int grid = tp.q > 1 ? tp.n_full : sp.grid;
     const int n_full = tp.q > 1 ? tp.n_full : sp.n_full;
     if (grid > 0) {
-        if (ragged)
+        if (krag)
             launch_whole<RK, TWO_FOUR, true, PASS2, false>(a, st, ldb, grid, tiles_m, tiles_n, n_full, sp.split,
                                                            part);
         else if (fold)
@@ -639,35 +644,38 @@ hipError_t launch_ranks(const LayerArgs& a, hipStream_t st, bool pass2, int ldb)
 #else  // LORS_THIN_TILES
 
 // thin tiles of one feature half (NF = 1) and TM tokens: 2 BM / TM per tile
-template <int RK, bool TWO_FOUR, bool FOLD, int TM>
+template <int RK, bool TWO_FOUR, bool KRAG, bool FOLD, int TM>
 hipError_t launch_thin_tm(const LayerArgs& a, hipStream_t st, int ldb, int first, int tail) {
     const int tiles_m = (int)((a.L + BM - 1) / BM);
     const int tiles_n = (int)((a.R + BN - 1) / BN);
-    hipLaunchKernelGGL((fwd_kernel<RK, TWO_FOUR, false, false, FOLD, TM, 1>), dim3(tail * (2 * BM / TM)), dim3(NT), 0, st,
+    hipLaunchKernelGGL((fwd_kernel<RK, TWO_FOUR, KRAG, false, FOLD, TM, 1>), dim3(tail * (2 * BM / TM)), dim3(NT), 0, st,
                        (const uint16_t*)a.X, (const uint16_t*)a.W, a.M, (const uint16_t*)a.B,
                        (const uint16_t*)a.A, (const uint16_t*)a.bias, (uint16_t*)a.Y, a.L, (int)a.R, (int)a.C,
                        (int)a.r, a.scale, tiles_m, tiles_n, ldb, first, tail, (float*)nullptr);
     return hipGetLastError();
 }
 
-template <int RK, bool TWO_FOUR, bool FOLD>
+template <int RK, bool TWO_FOUR, bool KRAG, bool FOLD>
 hipError_t launch_thin_q(const LayerArgs& a, hipStream_t st, int ldb, int first, int tail, int q) {
     switch (q) {  // q thin tiles per tile: two feature halves, each cut into q/2 token parts
-        case 2: return launch_thin_tm<RK, TWO_FOUR, FOLD, BM>(a, st, ldb, first, tail);
-        case 4: return launch_thin_tm<RK, TWO_FOUR, FOLD, BM / 2>(a, st, ldb, first, tail);
-        case 8: return launch_thin_tm<RK, TWO_FOUR, FOLD, BM / 4>(a, st, ldb, first, tail);
+        case 2: return launch_thin_tm<RK, TWO_FOUR, KRAG, FOLD, BM>(a, st, ldb, first, tail);
+        case 4: return launch_thin_tm<RK, TWO_FOUR, KRAG, FOLD, BM / 2>(a, st, ldb, first, tail);
+        case 8: return launch_thin_tm<RK, TWO_FOUR, KRAG, FOLD, BM / 4>(a, st, ldb, first, tail);
         default: return hipErrorInvalidValue;
     }
 }
 
 template <int RK>
 hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int ldb, int first, int tail, int q) {
-    const bool fold = power_of_two(a.scale);
+    const bool krag = !fwd_fixed_copies(a.C);
+    const bool fold = !krag && power_of_two(a.scale);
     if (a.two_four)
-        return fold ? launch_thin_q<RK, true, true>(a, st, ldb, first, tail, q)
-                    : launch_thin_q<RK, true, false>(a, st, ldb, first, tail, q);
-    return fold ? launch_thin_q<RK, false, true>(a, st, ldb, first, tail, q)
-                : launch_thin_q<RK, false, false>(a, st, ldb, first, tail, q);
+        return krag   ? launch_thin_q<RK, true, true, false>(a, st, ldb, first, tail, q)
+               : fold ? launch_thin_q<RK, true, false, true>(a, st, ldb, first, tail, q)
+                      : launch_thin_q<RK, true, false, false>(a, st, ldb, first, tail, q);
+    return krag   ? launch_thin_q<RK, false, true, false>(a, st, ldb, first, tail, q)
+           : fold ? launch_thin_q<RK, false, false, true>(a, st, ldb, first, tail, q)
+                  : launch_thin_q<RK, false, false, false>(a, st, ldb, first, tail, q);
 }
 
 #endif  // LORS_THIN_TILES
@@ -701,7 +709,7 @@ hipError_t launch_fwd_bf16(const LayerArgs& a, hipStream_t st) {
 
 hipError_t launch_fwd_thin_bf16(const LayerArgs& a, hipStream_t st, int ldb, int first, int tail, int q) {
     if (tail <= 0) return hipSuccess;
-    if (!fwd_whole_tiles(a.L, a.R, a.C) || a.r < 1 || a.r > 64) return hipErrorInvalidValue;
+    if (a.r < 1 || a.r > 64) return hipErrorInvalidValue;
     switch ((a.r + 15) / 16) {
         case 1: return launch_thin_rk<1>(a, st, ldb, first, tail, q);
         case 2: return launch_thin_rk<2>(a, st, ldb, first, tail, q);

@@ -46,10 +46,17 @@ constexpr int EP_B = 12288;                        // B block [i][32*JB] bf16: 1
 constexpr int EP_A = SMEM;                         // A block [32 j'][256 j]: 16 KiB
 constexpr int SMEM_ALL = SMEM + 32 * kRowBytes;
 
-// RAGGED: some tile reaches past R, C or the token count L (copies check
-// every lane and read the zero page outside the tensors); otherwise copies
-// use uniform bases plus fixed per-lane offsets.
-template <int RK, bool RAGGED>
+// Copies use uniform bases plus fixed per-lane offsets.  Columns past R or C
+// are not read: their lanes copy the last chunk that exists, and the G entries
+// they lead to are dropped by the mask words (zero there) and the guarded
+// adds.  kOverlap (L no multiple of BK): the last K-step starts at L - BK, inside
+// the tensors, and the token rows that the step before it has already counted
+// are cleared in LDS once it landed; kWhole leaves the test for it out of the
+// loop (it costs 4 %: 772 against 811 us at 4096 x 14336, 8192 tokens, rank
+// 64).  kChecked (L < BK, or offsets beyond 32 bits): every copy checks its
+// lanes and reads the zero page outside the tensors.
+enum Tokens { kWhole, kOverlap, kChecked };
+template <int RK, Tokens TOK>
 __global__ __launch_bounds__(NT, 1) void g_kernel(
     const uint16_t* __restrict__ dY, const uint16_t* __restrict__ X,
     const uint32_t* __restrict__ Mt, const uint16_t* __restrict__ Bm,
@@ -81,7 +88,14 @@ __global__ __launch_bounds__(NT, 1) void g_kernel(
     const int64_t nk = nk32;
     const int i0 = tm * BM;
     const int j0 = tn * BN;
-    const int64_t kofs = (int64_t)kbeg * BK;
+    // first token of K-step kt of this workgroup, and the rows of the K-step
+    // at the end of the tokens that its predecessor has counted
+    auto token0 = [&](int64_t kt) {
+        const int64_t k0 = (kbeg + kt) * BK;
+        return TOK == kOverlap && k0 > L - BK ? L - BK : k0;
+    };
+    const int64_t k_end = (kbeg + nk) * BK;
+    const int overlap = TOK == kOverlap && k_end > L ? (int)(k_end - L) : 0;
     const int wprT = (R + 31) >> 5;  // words per row of M^T
 
     // ---- asynchronous slab copies: copy pair q of this wave fills tile row
@@ -96,15 +110,14 @@ __global__ __launch_bounds__(NT, 1) void g_kernel(
     for (int q = 0; q < LOADS; ++q) {
         const int row = 2 * (LOADS * wave + q) + h;
         const int lc = swz_chunk(row, pchunk);
-        offD[q] = (uint32_t)((row * R + lc * 8) * 2);
-        offX[q] = (uint32_t)((row * C + lc * 8) * 2);
+        offD[q] = (uint32_t)((row * R + min(lc * 8, R - 8 - i0)) * 2);
+        offX[q] = (uint32_t)((row * C + min(lc * 8, C - 8 - j0)) * 2);
     }
     const uint16_t* dYt = uniform_ptr(dY + i0);
     const uint16_t* Xt = uniform_ptr(X + j0);
     auto copy_pair = [&](int q, int64_t k0, uint32_t sb) {
-        k0 += kofs;
         const uint32_t da = sb + (LOADS * wave + q) * 1024, xa = da + TILEB;
-        if constexpr (!RAGGED) {
+        if constexpr (TOK != kChecked) {
             copy16s_to_lds(uniform_ptr(dYt + k0 * R), offD[q], da);
             copy16s_to_lds(uniform_ptr(Xt + k0 * C), offX[q], xa);
         } else {
@@ -159,11 +172,20 @@ __global__ __launch_bounds__(NT, 1) void g_kernel(
     static_assert(BK / 16 == 4 && LOADS == 8, "sub-step schedule below assumes 4 sub-steps, 8 copy pairs");
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
-        const int64_t k0 = (int64_t)(st < nk ? st : nk - 1) * BK;
+        const int64_t k0 = token0(st < nk ? st : nk - 1);
 #pragma unroll
         for (int q = 0; q < LOADS; ++q) copy_pair(q, k0, lds0 + st * STAGEB);
     }
     stage_barrier<2 * LOADS>();  // stage 0 landed everywhere; stage 1 may still fly
+    // clears the first `overlap` token rows of the stage at s (every wave)
+    auto clear_overlap = [&](uint8_t* s) {
+        for (int e = tid; e < overlap * (kRowBytes / 16); e += NT) {
+            *(u32x4*)(s + 16 * e) = zero_u32x4();
+            *(u32x4*)(s + TILEB + 16 * e) = zero_u32x4();
+        }
+        lds_barrier();
+    };
+    if (TOK == kOverlap && overlap > 0 && nk == 1) clear_overlap(smem);
 
     bf16x8 fa0[4], fb0[4], fa1[4], fb1[4];
     load_frags(fa0, fb0, smem, 0);
@@ -188,7 +210,7 @@ __global__ __launch_bounds__(NT, 1) void g_kernel(
             // buffer, st^1, is free since the last barrier, and the barrier
             // below waits for the copies; at kt = 0 the prologue issued all
             // of stage 1)
-            const int64_t k1 = (kt + 1 < nk ? kt + 1 : nk - 1) * BK;
+            const int64_t k1 = token0(kt + 1 < nk ? kt + 1 : nk - 1);
             const uint32_t sq1 = lds0 + (st ^ 1) * STAGEB;
             const uint8_t* s1 = sb + 16 * kRowBytes;
             u32x2 lo = {0u, 0u};
@@ -209,7 +231,8 @@ __global__ __launch_bounds__(NT, 1) void g_kernel(
         load_frags(fa1, fb1, sb, 3);
         mfma16(fa0, fb0);
         stage_barrier<0>();
-        const int64_t k0 = (kt + 2 < nk ? kt + 2 : nk - 1) * BK;
+        if (TOK == kOverlap && overlap > 0 && kt + 2 == nk) clear_overlap(smem + (st ^ 1) * STAGEB);
+        const int64_t k0 = token0(kt + 2 < nk ? kt + 2 : nk - 1);
         const uint32_t sbq = lds0 + st * STAGEB;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -445,16 +468,16 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st) {
     auto* X = (const uint16_t*)a.X;
     auto* B = (const uint16_t*)a.B;
     auto* A = (const uint16_t*)a.A;
-    // fixed-offset copies: whole tiles and K-steps, per-lane byte offsets
-    // (64 token rows of R or C) inside 32 bits
-    const bool ragged = a.R % BM != 0 || a.C % BN != 0 || a.L % BK != 0 ||
-                        (int64_t)BK * a.R * 2 >= (1ll << 31) || (int64_t)BK * a.C * 2 >= (1ll << 31);
-    if (ragged)
-        hipLaunchKernelGGL((g_kernel<RK, true>), grid, block, 0, st, dY, X, a.Mt, B, A, a.dB, a.dA, a.L,
-                           (int)a.R, (int)a.C, (int)a.r, a.scale, tiles_m, tiles_n, sp.n_full, sp.split);
-    else
-        hipLaunchKernelGGL((g_kernel<RK, false>), grid, block, 0, st, dY, X, a.Mt, B, A, a.dB, a.dA, a.L,
-                           (int)a.R, (int)a.C, (int)a.r, a.scale, tiles_m, tiles_n, sp.n_full, sp.split);
+    // fixed-offset copies: at least one whole K-step of tokens, per-lane byte
+    // offsets (64 token rows of R or C) inside 32 bits
+    const bool checked = a.L < BK || (int64_t)BK * a.R * 2 >= (1ll << 31) || (int64_t)BK * a.C * 2 >= (1ll << 31);
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, dY, X, a.Mt, B, A, a.dB, a.dA, a.L, (int)a.R, (int)a.C,
+                           (int)a.r, a.scale, tiles_m, tiles_n, sp.n_full, sp.split);
+    };
+    if (checked) run(g_kernel<RK, kChecked>);
+    else if (a.L % BK != 0) run(g_kernel<RK, kOverlap>);
+    else run(g_kernel<RK, kWhole>);
     return hipGetLastError();
 }
 

@@ -67,16 +67,20 @@ struct ThinPlan {
     int n_full, tail, q;
 };
 ThinPlan thin_plan(int64_t tiles);
-// Whether the forward (Y = X.W'^T, tiles over L x R, K = C) and the dX kernel
-// (dX = dY.W', tiles over L x C, K = R) take their fixed-offset copies: whole
-// 256 x 256 tiles and 64-wide K-steps, and per-lane byte offsets of 256 slab
-// rows inside 32 bits.  Thin tiles need them; other shapes run whole tiles
-// whose copies check every lane.
+// Shapes of whole tiles, which never split over K: 256 x 256 tiles and 64-wide
+// K-steps cover the forward's L x R, K = C (dX's L x C, K = R) exactly.
 inline bool fwd_whole_tiles(int64_t L, int64_t R, int64_t C) {
     return L % 256 == 0 && R % 256 == 0 && C % 64 == 0 && 256 * C * 2 < (1ll << 31);
 }
 inline bool dx_whole_tiles(int64_t L, int64_t R, int64_t C) {
     return L % 256 == 0 && C % 256 == 0 && R % 64 == 0 && 256 * R * 2 < (1ll << 31) && 64 * C * 2 < (1ll << 31);
+}
+// Whether the forward (dX) takes copies of a uniform base plus fixed per-lane
+// offsets: whole K-steps, and the byte offsets of 256 slab rows (dX: of 256 dY
+// rows and 64 W rows) inside 32 bits.
+inline bool fwd_fixed_copies(int64_t C) { return C % 64 == 0 && 256 * C * 2 < (1ll << 31); }
+inline bool dx_fixed_copies(int64_t R, int64_t C) {
+    return R % 64 == 0 && 256 * R * 2 < (1ll << 31) && 64 * C * 2 < (1ll << 31);
 }
 // out (rows x cols, bf16) on the split tiles = the sum of their pieces'
 // partials in piece order (+ bias[col] when bias is not null), rounded once.
@@ -90,8 +94,7 @@ hipError_t launch_fwd_bf16(const LayerArgs& a, hipStream_t s);
 hipError_t launch_fwd24_bf16(const LayerArgs& a, hipStream_t s);      // 2:4 mask, sparse MFMA, rank <= 64
 hipError_t launch_dx_bf16(const LayerArgs& a, hipStream_t s);
 // The thin tiles of a short last wave (see ThinPlan): logical tiles first ..
-// first+tail-1, each cut into q; single-pass ranks (a.r <= 64), whole-tile
-// shapes.  ldb: row stride of B; ra: rows of A that exist; clear: the launch
+// first+tail-1, each cut into q; single-pass ranks (a.r <= 64).  ldb: row stride of B; ra: rows of A that exist; clear: the launch
 // also clears dB and dA (it is the first of the dX launches).
 hipError_t launch_fwd_thin_bf16(const LayerArgs& a, hipStream_t s, int ldb, int first, int tail, int q);
 hipError_t launch_dx_thin_bf16(const LayerArgs& a, hipStream_t s, int ldb, int ra, int first, int tail, int q,

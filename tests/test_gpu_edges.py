@@ -1,0 +1,66 @@
+"""Edges of the output tiles and K-steps: token and feature counts that leave a
+part of a 256 x 256 tile, of a thin tile or of a 64-wide K-step empty.
+
+Rows and columns past the tensors are copied from the last one that exists, so
+every output at an edge is compared with the oracle on its own tile (2e-2, the
+bar of the bf16 parity tests), W is unpruned with Inf and NaN at dropped
+positions, and the outputs sit between poisoned guards.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import lors as olors  # noqa: E402
+from paper_2501_08582_amd import ops, synth  # noqa: E402
+from gpu_helpers import TOL, dev_to_f64, to_dev, to_f64, unprune, worst_tile  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+FMT = {"magnitude": ops.BITMAP, "2:4": ops.TWO_FOUR}
+GUARD = 4096
+
+
+def _guarded(shape, dtype):
+    n = int(np.prod(shape)) * torch.tensor([], dtype=dtype).element_size()
+    buf = torch.full((2 * GUARD + n,), 0xA5, dtype=torch.uint8, device="cuda")
+    buf[GUARD:GUARD + n] = 0xFF  # NaN
+    return buf, buf[GUARD:GUARD + n].view(dtype).view(shape)
+
+
+# R, C multiples of 64: fixed copies in both directions; R or C % 64 = 8: the
+# last K-step of dX or the forward checks its lanes
+@pytest.mark.parametrize("R,C,L,r,mask,scale", [
+    (64, 64, 1, 16, "magnitude", 2.0),        # one token, one K-step, a quarter of a tile
+    (320, 192, 63, 5, "2:4", 2.0),            # below one token K-step of the weight gradient
+    (192, 448, 65, 16, "magnitude", 0.3),     # two token K-steps, 63 rows shared
+    (448, 576, 129, 40, "2:4", 0.5),
+    (264, 192, 200, 8, "magnitude", 2.0),     # dX: checked copies, thin
+    (192, 264, 321, 64, "magnitude", 1.5),    # forward: checked copies, thin
+    (1032, 1096, 130, 24, "2:4", 2.0),        # both, odd feature halves
+    (4160, 4224, 513, 16, "magnitude", 2.0),  # three token tiles, the last of one token
+    (256, 256, 300, 100, "magnitude", 2.0),   # ranks above 64
+])
+def test_edges(R, C, L, r, mask, scale):
+    name = "llama2_7b_up_proj_2_4" if mask == "2:4" else "llama2_7b_q_proj"
+    inp = synth.make(synth.workload(name).with_(R=R, C=C, r=r, scale=scale, seed=4000 + L), L=L)
+    inp.W = unprune(inp.W, inp.M, "bf16", seed=L)
+    X, W, B, A, dY = (to_dev(t, "bf16") for t in (inp.X, inp.W, inp.B, inp.A, inp.dY))
+    M = ops.mask_pack(torch.from_numpy(inp.M).cuda(), FMT[mask])
+    print("edges", (R, C, L, r, mask, scale), flush=True)
+    bufs = {"Y": _guarded((L, R), torch.bfloat16), "dX": _guarded((L, C), torch.bfloat16),
+            "dB": _guarded((R, r), torch.float32), "dA": _guarded((r, C), torch.float32)}
+    out = {k: v[1] for k, v in bufs.items()}
+    ops.forward(X, W, M, B, A, scale, FMT[mask], out=out["Y"])
+    ops.backward(dY, X, W, M, B, A, scale, FMT[mask], out=(out["dX"], out["dB"], out["dA"], None))
+    torch.cuda.synchronize()
+    x, w, b, a, dy = (to_f64(t, "bf16") for t in (inp.X, inp.W, inp.B, inp.A, inp.dY))
+    rdX, rdB, rdA, _ = olors.backward(dy, x, w, inp.M, b, a, scale)
+    want = {"Y": olors.forward(x, w, inp.M, b, a, scale), "dX": rdX, "dB": rdB, "dA": rdA}
+    for k, (buf, view) in bufs.items():
+        n = view.numel() * view.element_size()
+        assert torch.all(buf[:GUARD] == 0xA5) and torch.all(buf[GUARD + n:] == 0xA5), f"{k}: a guard byte changed"
+        got = dev_to_f64(view)
+        assert np.all(np.isfinite(got)), f"{k}: not finite"
+        err, at = worst_tile(got, want[k], (64, 64))
+        assert err <= TOL["bf16"], f"{k} block {at}: rel err {err:.3e}"
