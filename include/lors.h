@@ -37,11 +37,6 @@
  * rounded once to bf16 (nearest-even) before the main product; all products
  * accumulate in fp32; Y and dX are rounded to bf16 (nearest-even); G is
  * rounded to bf16 before the two rank-r products; dA, dB, dbias stay fp32.
- * For 64 < r <= 128 the forward and dX use that the mask
- * distributes over the adapter's rank blocks: Y (and dX) is the bf16 sum of
- * the product with select(M, W + s.B[:, :64].A[:64, :]) and the product with
- * select(M, s.B[:, 64:].A[64:, :]), each merged weight rounded once, so Y and
- * dX take one more bf16 rounding.
  * The fp32 dtype keeps every intermediate in fp32 (a debug/reference path).
  *
  * Ownership: the caller owns every buffer.  The library never allocates
@@ -133,12 +128,12 @@ typedef enum lors_mask_format {
 /* Forward and backward calls: when the forward's or dX's grid of 256 x 256
  * output tiles ends in a partial wave that fills at most half of the GPU's
  * compute units (e.g. 320 tiles on 256 CUs), that wave is spread over more
- * CUs.  On shapes of whole tiles (L and the output features multiples of
- * 256, the contraction a multiple of 64) this happens with or without the
- * flag and needs no workspace: each tile of the wave is cut over its tokens
- * into 2, 4 or 8 thin tiles, which compute the same bits as the whole tile.
- * On other shapes, with this flag, the tiles of that wave are cut
- * along their contraction (K) into up to 8 pieces, one per CU.  Each piece
+ * CUs.  Without the flag, and on shapes of whole tiles (L and the output
+ * features multiples of 256, the contraction a multiple of 64) with it, this
+ * needs no workspace: each tile of the wave is cut into its feature halves
+ * and over its tokens into 2, 4 or 8 thin tiles, which compute the same bits
+ * as the whole tile.  On other shapes, with this flag, the tiles of that wave
+ * are cut along their contraction (K) into up to 8 pieces, one per CU.  Each piece
  * writes its fp32 partial sums (256 KiB) to the workspace; a small reduction
  * launch adds a tile's pieces in a fixed order, adds the bias and rounds
  * once to bf16, so results stay bitwise reproducible.  The partials are
@@ -148,8 +143,8 @@ typedef enum lors_mask_format {
  * every tile of the short wave, fewer pieces are used, or none (the call
  * then runs as without the flag).  lors_workspace_bytes accounts for the
  * partials, and lors_forward requires a workspace when there are any.  No
- * effect for fp32; applies to ranks up to 64 (above, the layer already runs
- * as two passes).  The weight gradient always splits such a wave, with no
+ * effect for fp32; applies to ranks up to 64 (above, every tile runs as thin
+ * tiles).  The weight gradient always splits such a wave, with no
  * workspace: its pieces' partial G tiles go through the same rank-r products
  * and atomics as whole tiles. */
 #define LORS_FLAG_SPLIT_LAST_WAVE 0x8u

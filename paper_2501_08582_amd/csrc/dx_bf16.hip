@@ -25,8 +25,8 @@
 // resident A operand is pre-scaled by s, the rank-r MFMA accumulates onto W
 // (read, for the next stage, as soon as the wave's own W copies landed), and
 // a merge piece is the rounding and the select.
-// Works on ranks that are multiples of 8, up to 64 per pass (the launcher pads
-// other ranks with a zero-filled copy of B and splits larger ones in two).
+// Works on ranks that are multiples of 8 (the launcher pads other ranks with a
+// zero-filled copy of B); ranks above 64 as half-feature tiles only.
 #include "gemm_common.hpp"
 #include "kernels.hpp"
 
@@ -44,7 +44,7 @@ constexpr int GROUP_M = 4;
 constexpr int kEarly = 12;  // copies of a stage issued right after the barrier; the rest a sub-step later
 
 // B slab [k][rank]: 64 rows of PITCH = 32*RKP bytes (ranks padded to 16*RKP;
-// RKP = RK, except 4 for RK = 3 so that a row holds a power of two of 16-byte
+// RKP = RK rounded up to a power of two, so that a row holds a power of two of 16-byte
 // chunks).  Chunk q of row k is stored at chunk q ^ bswz(k): the merge reads
 // one chunk of 16 consecutive rows per 16 lanes, and with rows 32*RKP bytes
 // apart those rows would fall on only 8 / RKP of the 16 bank groups; the XOR
@@ -65,22 +65,26 @@ struct Layout {
     static constexpr int WB = 4 * WBW;             // W slab
     static constexpr int MB = FT * 2 * 4;          // M^T words [n][kb]
     static constexpr int DB = TM * kRow64;         // dY slab: TM rows of 64 k
-    static constexpr int RKP = RK == 3 ? 4 : RK;
+    static constexpr int RKP = RK == 3 ? 4 : RK > 4 ? 8 : RK;
     static constexpr int PITCH = 32 * RKP;
     static constexpr int BB = BK * PITCH;          // B slab: 2 KiB per 16 ranks
     static constexpr int D = 0, W = DB, B = DB + WB, M = DB + WB + BB;
     static constexpr int STAGE = DB + WB + BB + MB;
-    static constexpr int LUT = 2 * STAGE;          // select table: 16 x 8 B
-    static constexpr int SINK = LUT + 256;         // 1 KiB target of padding copies
-    static constexpr int TOTAL = SINK + 1024;
     static constexpr int NBC = BB / 1024;          // 1 KiB copies per B slab
     static constexpr int NB = (NBC + 3) / 4;       // B-slab copies per wave
+    static constexpr int PAD = NBC % 4 ? 1024 : 0; // target of the B slab's padding copies, where it has any
+    static constexpr int S = stages_that_fit(STAGE, 256 + PAD);
+    static constexpr int LUT = S * STAGE;          // select table: 16 x 8 B
+    static constexpr int SINK = LUT + 256;
+    static constexpr int TOTAL = SINK + PAD;
     static constexpr int ND = TM / 32;             // dY-slab copies per wave
     static constexpr int NWC = WBW / 1024;         // W-block copies per wave
     static constexpr int NMC = NF;                 // M^T copies per wave
     static constexpr int COPIES = ND + NWC + NB + NMC;  // copies per wave per stage
     static constexpr int EARLY = COPIES < kEarly ? COPIES : kEarly;
+    static constexpr int FLY = (S - 2) * COPIES;  // copies of later stages in flight at a K-step's barrier
     static_assert(COPIES - EARLY <= 8, "the late copies fit the eight merge slots");
+    static_assert(FLY + COPIES < 64, "vmcnt range");
     // physical chunk of logical chunk q in B-slab row k
     static __device__ __forceinline__ int bswz(int k, int q) { return q ^ ((k / (8 / RKP)) & (2 * RKP - 1)); }
 };
@@ -93,28 +97,25 @@ struct Layout {
 // base plus fixed offsets.  KRAG: the last K-step reaches past R, or the
 // offsets exceed 32 bits; every copy then checks its lanes and reads the zero
 // page outside the tensors.
-// PASS2: the second pass of a rank above 64 (ranks 64.. of B and A): W is
-// taken as zero and the product is added onto dX.  ldb: row stride of B.
 // r: the rank the kernel works on, a multiple of 8 (B's columns ra .. r-1
 // are zero); ra: the rows of A that exist (A rows ra .. r-1 are read as zero).
-// TM, NF < (BM, 2): a thin tile of TM tokens and 128 NF input features (one
-// pass), as in the forward kernel.
-template <int RK, bool KRAG, bool PASS2, bool FOLD, int TM, int NF>
+// TM, NF < (BM, 2): a thin tile of TM tokens and 128 NF input features, as in
+// the forward kernel.
+template <int RK, bool KRAG, bool FOLD, int TM, int NF>
 __global__ __launch_bounds__(NT, 1) void dx_kernel(
     const uint16_t* __restrict__ dY, const uint16_t* __restrict__ W,
     const uint32_t* __restrict__ Mt, const uint16_t* __restrict__ Bm,
     const uint16_t* __restrict__ Am, uint16_t* __restrict__ dX, int64_t L, int R, int C, int r,
-    int ra, float s, int tiles_m, int tiles_n, int ldb, float* __restrict__ z0, int64_t nz0,
+    int ra, float s, int tiles_m, int tiles_n, float* __restrict__ z0, int64_t nz0,
     float* __restrict__ z1, int64_t nz1, int n_full, int split, float* __restrict__ part) {
     using Lay = Layout<RK, TM, NF>;
     constexpr int MBW = TM / 32;  // 32-token blocks per wave
-    static_assert((TM == BM && NF == 2) || !PASS2, "thin tiles: one pass");
+    static_assert(NF == 1 || RK <= 4, "ranks above 64: half-feature tiles");
     static_assert(Lay::TOTAL <= 160 * 1024, "LDS budget");
-    static_assert(4 * TM * 64 * NF <= 2 * Lay::STAGE, "output staging fits the stage buffers");
-    // the prologue parks the merge's A block in stage 1: in its dY region,
-    // clear of the W slabs that PASS2 zeroes once (a thin tile's dY region is
-    // smaller, but it has no second pass and may use the whole stage)
-    static_assert(16 * RK * kRowBytes <= (PASS2 ? Lay::DB : Lay::STAGE), "A block fits stage 1");
+    static_assert(4 * TM * 64 * NF <= Lay::S * Lay::STAGE, "output staging fits the stage buffers");
+    // the prologue parks the merge's A block in the last PARK stages
+    constexpr int PARK = (16 * RK * kRowBytes + Lay::STAGE - 1) / Lay::STAGE;
+    static_assert(PARK < Lay::S, "A block fits beside stage 0");
     __shared__ __attribute__((aligned(1024))) uint8_t smem[Lay::TOTAL];
 
     const int tid = threadIdx.x;
@@ -165,8 +166,7 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
     const uint8_t* zsrc = (const uint8_t*)g_zero_page + 16 * lane;
     // B-slab copy q of this wave lands at slab byte 1024*(4q + wave) + 16*lane,
     // i.e. row brow[q], physical chunk p; it carries logical chunk
-    // bswz(brow, p) -- ranks 8*that .. +7 of B row k0 + brow[q] (rows of B are
-    // ldb elements apart in memory), zeros for ranks at or past r
+    // bswz(brow, p) -- ranks 8*that .. +7 of B row k0 + brow[q] zeros for ranks at or past r
     int brow[Lay::NB], bcol[Lay::NB];
     bool bval[Lay::NB];
 #pragma unroll
@@ -231,7 +231,6 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
                 copy16_to_lds(ok ? (const void*)(Dt + (int64_t)row * R + k0 + 8 * lc) : (const void*)zsrc, dst);
             }
         } else if (j < Lay::ND + Lay::NWC) {
-            if (PASS2) return;  // W is zero: its slabs were cleared once
             const int q = j - Lay::ND;
             const uint32_t dst = sb + Lay::W + Lay::WBW * wave + 1024 * q;
             if constexpr (!KRAG) {
@@ -248,7 +247,7 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
             const int q = j - Lay::ND - Lay::NWC, blk = 4 * q + wave;
             const bool real = blk < Lay::NBC;
             const bool ok = bval[q] && (!KRAG || k0 + brow[q] < R);
-            const void* src = (const uint8_t*)Bm + ((int64_t)k0 + brow[q]) * (2 * (int64_t)ldb) + bcol[q];
+            const void* src = (const uint8_t*)Bm + ((int64_t)k0 + brow[q]) * (2 * (int64_t)r) + bcol[q];
             copy16_to_lds(ok ? src : (const void*)zsrc, real ? sb + Lay::B + 1024 * blk : lds0 + Lay::SINK);
         } else {
             const int q = j - Lay::ND - Lay::NWC - Lay::NB;
@@ -412,7 +411,7 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
             read_d2(dn, sb, c4n, i);
             if (c4n == 1) { unpack(rwa, 0, 2 * i); unpack(rwa, 0, 2 * i + 1); }
             if (c4n == 3 && i == 3) {
-                wait_vmcnt<Lay::NB + Lay::NMC>();  // this wave's W copies of the next stage
+                wait_vmcnt<Lay::NB + Lay::NMC + Lay::FLY>();  // this wave's W copies of the next stage
                 read_raw(rwa, snext, 0);
                 read_raw(rwb, snext, 1);
             }
@@ -433,17 +432,13 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
         SLOT_END();
     };
 
-    if constexpr (PASS2) {  // W taken as zero: clear both W slabs once, never copy them
-        for (int i = tid; i < 2 * (Lay::WB / 16); i += NT)
-            *(u32x4*)(smem + (i / (Lay::WB / 16)) * Lay::STAGE + Lay::W + 16 * (i % (Lay::WB / 16))) = zero_u32x4();
-        __syncthreads();
-    }
-
-    // ---- prologue.  The A block of the merge goes to stage 1's dY region
-    // while stage 0 is copied; once both landed, the A block is read into
-    // registers and stage 1 is copied over it (the first K-step's barrier
-    // waits for stage 1), so the two round trips to memory overlap.
-    // A[:, n0 .. n0+255] (16*RK rows) -> stage 1's dY region
+    // ---- prologue.  The A block of the merge goes to the last PARK stages'
+    // buffers while the stages before them are copied; once it and stage 0
+    // landed, the A block is read into registers and those stages are copied
+    // over it (the K-steps' barriers wait for them), so the two round trips to
+    // memory overlap.
+    // A[:, n0 .. n0+255] (16*RK rows)
+    constexpr int kPark = (Lay::S - PARK) * Lay::STAGE;
 #pragma unroll
     for (int q = 0; q < 2 * RK; ++q) {
         const int blk = 4 * q + wave;
@@ -451,18 +446,20 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
         const int lc = swz_chunk(row, lane & 31);
         const int gn = n0 + 8 * lc;
         copy16_to_lds((row < ra && gn < C) ? (const void*)(Am + (int64_t)row * C + gn) : (const void*)zsrc,
-                      lds0 + Lay::STAGE + 1024 * blk);
+                      lds0 + kPark + 1024 * blk);
     }
 #pragma unroll
-    for (int j = 0; j < Lay::COPIES; ++j) copy_j(j, 0, lds0);
-    stage_barrier<0>();
+    for (int i = 0; i < Lay::S - PARK; ++i)
+#pragma unroll
+        for (int j = 0; j < Lay::COPIES; ++j) copy_j(j, (i < nk ? i : nk - 1) * BK, lds0 + i * Lay::STAGE);
+    stage_barrier<(Lay::S - PARK - 1) * Lay::COPIES>();
     // the merge's B operand A[16c + 8h + e][n] into registers via transpose loads
 #pragma unroll
     for (int nb = 0; nb < NF; ++nb)
 #pragma unroll
         for (int c = 0; c < RK; ++c)
-            afr[nb][c] = frag_from_tr(lds_tr_read(smem + Lay::STAGE + tr_frag_off(lane, 16 * c, 32 * NF * wave + 32 * nb, 0)),
-                                      lds_tr_read(smem + Lay::STAGE + tr_frag_off(lane, 16 * c, 32 * NF * wave + 32 * nb, 1)));
+            afr[nb][c] = frag_from_tr(lds_tr_read(smem + kPark + tr_frag_off(lane, 16 * c, 32 * NF * wave + 32 * nb, 0)),
+                                      lds_tr_read(smem + kPark + tr_frag_off(lane, 16 * c, 32 * NF * wave + 32 * nb, 1)));
     if constexpr (FOLD) {  // s.A, exact for a power-of-two s
 #pragma unroll
         for (int nb = 0; nb < NF; ++nb)
@@ -477,7 +474,9 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
     }
     lds_barrier();
 #pragma unroll
-    for (int j = 0; j < Lay::COPIES; ++j) copy_j(j, nk > 1 ? BK : 0, lds0 + Lay::STAGE);
+    for (int i = Lay::S - PARK; i < Lay::S; ++i)
+#pragma unroll
+        for (int j = 0; j < Lay::COPIES; ++j) copy_j(j, (i < nk ? i : nk - 1) * BK, lds0 + i * Lay::STAGE);
     read_mw(smem);
     read_bfr(smem, 0);
     if constexpr (FOLD) {
@@ -503,25 +502,26 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
     }
 
     // ---- main loop (branch-free, see the forward kernel)
-    for (int kt = 0; kt < nk; ++kt) {
-        const int st = kt & 1;
+    for (int kt = 0, st = 0; kt < nk; ++kt) {
+        constexpr int S = Lay::S;
+        const int sx = st + 1 < S ? st + 1 : 0;  // buffers of K-steps kt+1 and kt-1
+        const int sp = st > 0 ? st - 1 : S - 1;
         const uint8_t* sb = smem + st * Lay::STAGE;
-        const uint8_t* sn = smem + (st ^ 1) * Lay::STAGE;
-        // copies EARLY.. of stage kt+1 (buffer st^1, free since the last
-        // barrier; the barrier below waits for them); at kt = 0 the prologue
-        // issued all of stage 1
-        const int k1 = (kt + 1 < nk ? kt + 1 : nk - 1) * BK;
+        const uint8_t* sn = smem + sx * Lay::STAGE;
+        // copies EARLY.. of stage kt+S-1 (buffer sp, free since the last
+        // barrier); at kt = 0 the prologue issued all of them
+        const int k1 = (kt + S - 1 < nk ? kt + S - 1 : nk - 1) * BK;
         if constexpr (FOLD) {
-            substep_fold(da, wa, db, wb, sb, sn, 1, k1, lds0 + (st ^ 1) * Lay::STAGE, kt > 0);
+            substep_fold(da, wa, db, wb, sb, sn, 1, k1, lds0 + sp * Lay::STAGE, kt > 0);
             substep_fold(db, wb, da, wa, sb, sn, 2);
             substep_fold(da, wa, db, wb, sb, sn, 3);
         } else {
-            substep(da, wa, db, wb, sb, 1, std::true_type{}, k1, lds0 + (st ^ 1) * Lay::STAGE, kt > 0);
+            substep(da, wa, db, wb, sb, 1, std::true_type{}, k1, lds0 + sp * Lay::STAGE, kt > 0);
             substep(db, wb, da, wa, sb, 2, std::false_type{});
             substep(da, wa, db, wb, sb, 3, std::false_type{});
         }
-        stage_barrier<0>();
-        const int k2 = (kt + 2 < nk ? kt + 2 : nk - 1) * BK;
+        stage_barrier<Lay::FLY>();  // the FLY copies issued last belong to later stages
+        const int k2 = (kt + S < nk ? kt + S : nk - 1) * BK;
         const uint32_t sq = lds0 + st * Lay::STAGE;
         // one copy per MFMA slot: a copy issued behind an MFMA stalls the
         // wave while that MFMA runs, a second one would stall the next
@@ -551,6 +551,7 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
         }
         mm(15, db, wb);
         SLOT_END();
+        st = sx;
     }
     // ---- epilogue: round to bf16, stage the wave's TM x 32 NF block in LDS
     // (rows of 32 NF outputs), then 16-byte stores of whole rows.
@@ -586,12 +587,7 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
         const u32x4 v = *(const u32x4*)(ol + row * OW + 8 * ch);
         const int64_t gm = m0 + row;
         const int gn = n0 + OW * wave + 8 * ch;
-        if (gm < L && gn < C) {
-            if constexpr (PASS2)
-                *(u32x4*)(dX + gm * C + gn) = add_bf16x8(*(const u32x4*)(dX + gm * C + gn), v);
-            else
-                *(u32x4*)(dX + gm * C + gn) = v;
-        }
+        if (gm < L && gn < C) *(u32x4*)(dX + gm * C + gn) = v;
     }
 }
 
@@ -603,32 +599,33 @@ bool power_of_two(float s) {
 }
 
 // z0, z1: dB (R x rank) and dA (rank x C) to clear, or null
-template <int RK, bool KRAG, bool PASS2, bool FOLD, int TM, int NF>
-void launch_tm(const LayerArgs& a, hipStream_t st, int ldb, int ra, int grid, int tiles_m, int tiles_n, int n_full,
+template <int RK, bool KRAG, bool FOLD, int TM, int NF>
+void launch_tm(const LayerArgs& a, hipStream_t st, int ra, int grid, int tiles_m, int tiles_n, int n_full,
                int split, float* part, float* z0, int64_t nz0, float* z1, int64_t nz1) {
-    hipLaunchKernelGGL((dx_kernel<RK, KRAG, PASS2, FOLD, TM, NF>), dim3(grid), dim3(NT), 0, st, (const uint16_t*)a.dY,
+    hipLaunchKernelGGL((dx_kernel<RK, KRAG, FOLD, TM, NF>), dim3(grid), dim3(NT), 0, st, (const uint16_t*)a.dY,
                        (const uint16_t*)a.W, a.Mt, (const uint16_t*)a.B, (const uint16_t*)a.A, (uint16_t*)a.dX, a.L,
-                       (int)a.R, (int)a.C, (int)a.r, ra, a.scale, tiles_m, tiles_n, ldb, z0, nz0, z1, nz1, n_full,
+                       (int)a.R, (int)a.C, (int)a.r, ra, a.scale, tiles_m, tiles_n, z0, nz0, z1, nz1, n_full,
                        split, part);
 }
 
 #ifndef LORS_THIN_TILES
 
-template <int RK, bool PASS2>
-hipError_t launch_rk(const LayerArgs& a, hipStream_t st, int ldb, int ra, bool clear) {
+// a.r: the (padded) rank; ra: the rows of A that exist.  The first launch
+// clears dB and dA when the caller asks for it (a.clear_grads).
+template <int RK>
+hipError_t launch_rk(const LayerArgs& a, hipStream_t st, int ra) {
     const int tiles_m = (int)((a.L + BM - 1) / BM);
     const int tiles_n = (int)((a.C + BN - 1) / BN);
     const int tiles = tiles_m * tiles_n;
     const bool krag = !dx_fixed_copies(a.R, a.C);
     const bool fold = !krag && power_of_two(a.scale);  // fixed-offset copies with a power-of-two scale
     // A short last wave is cut over K when the caller gave room for the
-    // pieces' partial sums (shapes without whole tiles, one pass only: ranks
-    // up to 64); otherwise it runs as thin tiles (the same bits as whole
+    // pieces' partial sums (shapes without whole tiles); otherwise it runs as thin tiles (the same bits as whole
     // ones, no workspace).
     TailSplit sp{tiles, 1, tiles};
-    if (a.split_ws != nullptr && !PASS2 && ldb <= 64 && !dx_whole_tiles(a.L, a.R, a.C))
+    if (a.split_ws != nullptr && !dx_whole_tiles(a.L, a.R, a.C))
         sp = tail_split(tiles, (a.R + BK - 1) / BK, a.split_budget);
-    const ThinPlan tp = (sp.split == 1 && !PASS2) ? thin_plan(tiles) : ThinPlan{tiles, 0, 1};
+    const ThinPlan tp = sp.split == 1 ? thin_plan(tiles) : ThinPlan{tiles, 0, 1};
     float* part = sp.split > 1 ? (float*)a.split_ws : nullptr;
     // with thin tiles the whole-tile grid is exactly the first n_full tiles
     // (work_coords regroups ids over the tiles it is told the grid holds)
@@ -636,75 +633,62 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st, int ldb, int ra, bool c
     const int n_full = tp.q > 1 ? tp.n_full : sp.n_full;
     // clear: dB (R x rank) and dA (rank x C) of the caller's problem, by the
     // first launch of this call
-    const bool clear_here = clear && grid > 0;
+    const bool clear_here = a.clear_grads && grid > 0;
     float* z0 = clear_here ? a.dB : nullptr;
     float* z1 = clear_here ? a.dA : nullptr;
     const int64_t nz0 = clear_here ? a.R * a.r_grad : 0, nz1 = clear_here ? a.r_grad * a.C : 0;
     if (grid > 0) {
         if (krag)
-            launch_tm<RK, true, PASS2, false, BM, 2>(a, st, ldb, ra, grid, tiles_m, tiles_n, n_full, sp.split, part, z0,
+            launch_tm<RK, true, false, BM, 2>(a, st, ra, grid, tiles_m, tiles_n, n_full, sp.split, part, z0,
                                                   nz0, z1, nz1);
         else if (fold)
-            launch_tm<RK, false, PASS2, true, BM, 2>(a, st, ldb, ra, grid, tiles_m, tiles_n, n_full, sp.split, part, z0,
+            launch_tm<RK, false, true, BM, 2>(a, st, ra, grid, tiles_m, tiles_n, n_full, sp.split, part, z0,
                                                   nz0, z1, nz1);
         else
-            launch_tm<RK, false, PASS2, false, BM, 2>(a, st, ldb, ra, grid, tiles_m, tiles_n, n_full, sp.split, part,
+            launch_tm<RK, false, false, BM, 2>(a, st, ra, grid, tiles_m, tiles_n, n_full, sp.split, part,
                                                    z0, nz0, z1, nz1);
     }
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && tp.q > 1)
-        e = launch_dx_thin_bf16(a, st, ldb, ra, tp.n_full, tp.tail, tp.q, clear && !clear_here);
+        e = launch_dx_thin_bf16(a, st, ra, tp.n_full, tp.tail, tp.q, a.clear_grads && !clear_here);
     if (e == hipSuccess && sp.split > 1)
         e = launch_split_reduce_bf16(part, sp.n_full, sp.split, tiles_m, tiles_n, GROUP_M, a.L, (int)a.C, nullptr,
                                      a.dX, st);
     return e;
 }
 
-// a.r: the (padded) rank of this pass; ra: the rows of A that exist
-// The first pass clears dB and dA when the caller asks for it (a.clear_grads).
-hipError_t launch_ranks(const LayerArgs& a, hipStream_t st, bool pass2, int ldb, int ra) {
-    const bool c = a.clear_grads && !pass2;
-    switch ((a.r + 15) / 16) {
-        case 1: return pass2 ? launch_rk<1, true>(a, st, ldb, ra, false) : launch_rk<1, false>(a, st, ldb, ra, c);
-        case 2: return pass2 ? launch_rk<2, true>(a, st, ldb, ra, false) : launch_rk<2, false>(a, st, ldb, ra, c);
-        case 3: return pass2 ? launch_rk<3, true>(a, st, ldb, ra, false) : launch_rk<3, false>(a, st, ldb, ra, c);
-        case 4: return pass2 ? launch_rk<4, true>(a, st, ldb, ra, false) : launch_rk<4, false>(a, st, ldb, ra, c);
-        default: return hipErrorInvalidValue;
-    }
-}
-
 #else  // LORS_THIN_TILES
 
 // thin tiles of one feature half (NF = 1) and TM tokens: 2 BM / TM per tile
 template <int RK, bool KRAG, bool FOLD, int TM>
-hipError_t launch_thin_tm(const LayerArgs& a, hipStream_t st, int ldb, int ra, int first, int tail, bool clear) {
+hipError_t launch_thin_tm(const LayerArgs& a, hipStream_t st, int ra, int first, int tail, bool clear) {
     const int tiles_m = (int)((a.L + BM - 1) / BM);
     const int tiles_n = (int)((a.C + BN - 1) / BN);
     float* z0 = clear ? a.dB : nullptr;
     float* z1 = clear ? a.dA : nullptr;
     const int64_t nz0 = clear ? a.R * a.r_grad : 0, nz1 = clear ? a.r_grad * a.C : 0;
-    launch_tm<RK, KRAG, false, FOLD, TM, 1>(a, st, ldb, ra, tail * (2 * BM / TM), tiles_m, tiles_n, first, tail, nullptr,
+    launch_tm<RK, KRAG, FOLD, TM, 1>(a, st, ra, tail * (2 * BM / TM), tiles_m, tiles_n, first, tail, nullptr,
                                           z0, nz0, z1, nz1);
     return hipGetLastError();
 }
 
 template <int RK, bool KRAG, bool FOLD>
-hipError_t launch_thin_q(const LayerArgs& a, hipStream_t st, int ldb, int ra, int first, int tail, int q,
+hipError_t launch_thin_q(const LayerArgs& a, hipStream_t st, int ra, int first, int tail, int q,
                          bool clear) {
     switch (q) {  // q thin tiles per tile: two feature halves, each cut into q/2 token parts
-        case 2: return launch_thin_tm<RK, KRAG, FOLD, BM>(a, st, ldb, ra, first, tail, clear);
-        case 4: return launch_thin_tm<RK, KRAG, FOLD, BM / 2>(a, st, ldb, ra, first, tail, clear);
-        case 8: return launch_thin_tm<RK, KRAG, FOLD, BM / 4>(a, st, ldb, ra, first, tail, clear);
+        case 2: return launch_thin_tm<RK, KRAG, FOLD, BM>(a, st, ra, first, tail, clear);
+        case 4: return launch_thin_tm<RK, KRAG, FOLD, BM / 2>(a, st, ra, first, tail, clear);
+        case 8: return launch_thin_tm<RK, KRAG, FOLD, BM / 4>(a, st, ra, first, tail, clear);
         default: return hipErrorInvalidValue;
     }
 }
 
 template <int RK>
-hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int ldb, int ra, int first, int tail, int q,
+hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int ra, int first, int tail, int q,
                           bool clear) {
-    if (!dx_fixed_copies(a.R, a.C)) return launch_thin_q<RK, true, false>(a, st, ldb, ra, first, tail, q, clear);
-    return power_of_two(a.scale) ? launch_thin_q<RK, false, true>(a, st, ldb, ra, first, tail, q, clear)
-                                 : launch_thin_q<RK, false, false>(a, st, ldb, ra, first, tail, q, clear);
+    if (!dx_fixed_copies(a.R, a.C)) return launch_thin_q<RK, true, false>(a, st, ra, first, tail, q, clear);
+    return power_of_two(a.scale) ? launch_thin_q<RK, false, true>(a, st, ra, first, tail, q, clear)
+                                 : launch_thin_q<RK, false, false>(a, st, ra, first, tail, q, clear);
 }
 
 #endif  // LORS_THIN_TILES
@@ -713,16 +697,19 @@ hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int ldb, int ra, i
 
 #ifdef LORS_THIN_TILES
 
-hipError_t launch_dx_thin_bf16(const LayerArgs& a, hipStream_t st, int ldb, int ra, int first, int tail, int q,
-                               bool clear) {
+hipError_t launch_dx_thin_bf16(const LayerArgs& a, hipStream_t st, int ra, int first, int tail, int q, bool clear) {
     if (tail <= 0) return hipSuccess;
-    // a.r: this pass's rank, a multiple of 8 up to 64 (see launch_dx_bf16)
-    if (a.r < 8 || a.r > 64 || a.r % 8 != 0) return hipErrorInvalidValue;
+    // a.r: a multiple of 8 (see launch_dx_bf16)
+    if (a.r < 8 || a.r % 8 != 0) return hipErrorInvalidValue;
     switch ((a.r + 15) / 16) {
-        case 1: return launch_thin_rk<1>(a, st, ldb, ra, first, tail, q, clear);
-        case 2: return launch_thin_rk<2>(a, st, ldb, ra, first, tail, q, clear);
-        case 3: return launch_thin_rk<3>(a, st, ldb, ra, first, tail, q, clear);
-        case 4: return launch_thin_rk<4>(a, st, ldb, ra, first, tail, q, clear);
+        case 1: return launch_thin_rk<1>(a, st, ra, first, tail, q, clear);
+        case 2: return launch_thin_rk<2>(a, st, ra, first, tail, q, clear);
+        case 3: return launch_thin_rk<3>(a, st, ra, first, tail, q, clear);
+        case 4: return launch_thin_rk<4>(a, st, ra, first, tail, q, clear);
+        case 5: return launch_thin_rk<5>(a, st, ra, first, tail, q, clear);
+        case 6: return launch_thin_rk<6>(a, st, ra, first, tail, q, clear);
+        case 7: return launch_thin_rk<7>(a, st, ra, first, tail, q, clear);
+        case 8: return launch_thin_rk<8>(a, st, ra, first, tail, q, clear);
         default: return hipErrorInvalidValue;
     }
 }
@@ -736,27 +723,30 @@ hipError_t launch_dx_bf16(const LayerArgs& a, hipStream_t st) {
     // is not a multiple of 8 works on a copy of B whose rows are padded with
     // zero columns to rp = roundup8(r); the missing A rows are read as zero.
     LayerArgs ap = a;
-    const int rp = (int)((a.r + 7) / 8 * 8);
-    if (rp != a.r) {
+    const int ra = (int)a.r;
+    const int rp = (ra + 7) / 8 * 8;
+    if (rp != ra) {
         if (a.b_pad == nullptr) return hipErrorInvalidValue;
         const hipError_t e = launch_pad_cols_bf16(a.B, a.R, a.r, rp, a.b_pad, st);
         if (e != hipSuccess) return e;
         ap.B = a.b_pad;
         ap.r = rp;
     }
-    if (rp <= 64) return launch_ranks(ap, st, false, rp, (int)a.r);
-    // Ranks above 64: two passes over the ranks [0, 64) and [64, r), the
-    // second with W taken as zero and its product added onto dX (the mask
-    // distributes over the sum; one more bf16 rounding of dX).
-    LayerArgs a1 = ap;
-    a1.r = 64;
-    const hipError_t e = launch_ranks(a1, st, false, rp, 64);
-    if (e != hipSuccess) return e;
-    LayerArgs a2 = ap;
-    a2.r = rp - 64;
-    a2.B = (const uint16_t*)ap.B + 64;
-    a2.A = (const uint16_t*)a.A + 64 * a.C;
-    return launch_ranks(a2, st, true, rp, (int)a.r - 64);
+    switch ((rp + 15) / 16) {
+        case 1: return launch_rk<1>(ap, st, ra);
+        case 2: return launch_rk<2>(ap, st, ra);
+        case 3: return launch_rk<3>(ap, st, ra);
+        case 4: return launch_rk<4>(ap, st, ra);
+        default: break;
+    }
+    // ranks above 64: half-feature thin tiles only (see the forward)
+    int first[2], tail[2], q[2];
+    const int64_t tiles = ((a.L + BM - 1) / BM) * ((a.C + BN - 1) / BN);
+    const int n = thin_only_plan(tiles, first, tail, q);
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < n && e == hipSuccess; ++i)
+        e = launch_dx_thin_bf16(ap, st, ra, first[i], tail[i], q[i], a.clear_grads && i == 0);
+    return e;
 }
 
 #endif  // LORS_THIN_TILES

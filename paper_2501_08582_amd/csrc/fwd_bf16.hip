@@ -69,16 +69,20 @@ struct Layout {
     static constexpr int AB = 16 * RK * kRow64;   // A slab: 16*RK rows of 64 k
     static constexpr int X = 0, W = XB, A = XB + WB, M = XB + WB + AB;
     static constexpr int STAGE = XB + WB + AB + MB;
-    static constexpr int LUT = 2 * STAGE;         // select table: 16 x 8 B
-    static constexpr int SINK = LUT + 256;        // 1 KiB target of padding copies
-    static constexpr int TOTAL = SINK + 1024;
+    static constexpr int PAD = 2 * RK % 4 ? 1024 : 0;  // target of the A slab's padding copies, where it has any
+    static constexpr int S = stages_that_fit(STAGE, 256 + PAD);
+    static constexpr int LUT = S * STAGE;         // select table: 16 x 8 B
+    static constexpr int SINK = LUT + 256;
+    static constexpr int TOTAL = SINK + PAD;
     static constexpr int NX = TM / 32;            // X-slab copies per wave
     static constexpr int NWC = 4 * NF;            // W-slab copies per wave
     static constexpr int NAW = (2 * RK + 3) / 4;  // A-slab copies per wave
     static constexpr int NMC = NF;                // mask copies per wave
     static constexpr int COPIES = NX + NWC + NAW + NMC;  // copies per wave per stage
     static constexpr int EARLY = COPIES < kEarly ? COPIES : kEarly;
+    static constexpr int FLY = (S - 2) * COPIES;  // copies of later stages in flight at a K-step's barrier
     static_assert(COPIES - EARLY <= 8, "the late copies fit the eight merge slots");
+    static_assert(FLY + COPIES < 64, "vmcnt range");
 };
 
 #define SLOT_END() __builtin_amdgcn_sched_barrier(0)
@@ -94,25 +98,22 @@ struct Layout {
 // fixed offsets.  KRAG: the last K-step reaches past C, or the offsets exceed
 // 32 bits; every copy then checks its lanes and reads the zero page outside
 // the tensors.
-// PASS2: the second pass of a rank above 64 (ranks 64.. of B and A): W is
-// taken as zero and the product is added onto Y.  ldb: row stride of B.
-// TM, NF < (BM, 2): a thin tile of TM tokens and 128 NF features
-// (one pass); each wave then holds TM x 32 NF
+// TM, NF < (BM, 2): a thin tile of TM tokens and 128 NF features; each wave then holds TM x 32 NF
 // accumulators, merges 32 NF rows of W', and the MFMA slots, X reads and
 // merge pieces of the missing token and feature blocks drop out of the
 // schedule.
-template <int RK, bool TWO_FOUR, bool KRAG, bool PASS2, bool FOLD, int TM, int NF>
+template <int RK, bool KRAG, bool FOLD, int TM, int NF>
 __global__ __launch_bounds__(NT, 1) void fwd_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
     const uint32_t* __restrict__ Mp, const uint16_t* __restrict__ Bm,
     const uint16_t* __restrict__ Am, const uint16_t* __restrict__ bias,
     uint16_t* __restrict__ Y, int64_t L, int R, int C, int r, float s, int tiles_m,
-    int tiles_n, int ldb, int n_full, int split, float* __restrict__ part) {
+    int tiles_n, int n_full, int split, float* __restrict__ part, int two_four) {
     using Lay = Layout<RK, TM, NF>;
     constexpr int MBW = TM / 32;  // 32-token blocks per wave
-    static_assert((TM == BM && NF == 2) || !PASS2, "thin tiles: one pass");
+    static_assert(NF == 1 || RK <= 4, "ranks above 64: half-feature tiles");
     static_assert(Lay::TOTAL <= 160 * 1024, "LDS budget");
-    static_assert(4 * TM * 64 * NF <= 2 * Lay::STAGE, "output staging fits the stage buffers");
+    static_assert(4 * TM * 64 * NF <= Lay::S * Lay::STAGE, "output staging fits the stage buffers");
     __shared__ __attribute__((aligned(1024))) uint8_t smem[Lay::TOTAL];
 
     const int tid = threadIdx.x;
@@ -154,8 +155,9 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
     // ---- select table (visible to all waves after the first stage barrier)
     // and the resident B operand of the merge: column n = 64 wave + 32 nb + l32,
     // ranks 16c + 8h .. +7
-    if (tid < 16) *(u32x2*)(smem + Lay::LUT + 8 * tid) = select_lut16_entry<TWO_FOUR>((uint32_t)tid);
-    const bool b_vec = (r & 7) == 0 && (ldb & 7) == 0;
+    if (tid < 16) *(u32x2*)(smem + Lay::LUT + 8 * tid) = two_four ? select_lut16_entry<true>((uint32_t)tid)
+                                                              : select_lut16_entry<false>((uint32_t)tid);
+    const bool b_vec = (r & 7) == 0;
     bf16x8 bfr[NF][RK];
 #pragma unroll
     for (int nb = 0; nb < NF; ++nb) {
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
             u32x4 v = zero_u32x4();
             const int j0 = 16 * c + 8 * h;
             if (gn < R) {
-                const uint16_t* src = Bm + (int64_t)gn * ldb + j0;
+                const uint16_t* src = Bm + (int64_t)gn * r + j0;
                 if (b_vec) {
                     if (j0 < r) v = *(const u32x4*)src;
                 } else {
@@ -226,7 +228,6 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
         if (j < Lay::NX + Lay::NWC) {
             const bool isx = j < Lay::NX;
             const int q = isx ? j : j - Lay::NX;
-            if (PASS2 && !isx) return;  // W is zero: its slabs were cleared once
             const int blk = isx ? Lay::NX * wave + q : Lay::NWC * wave + q;
             const uint32_t dst = sb + (isx ? Lay::X : Lay::W) + 1024 * blk;
             if constexpr (!KRAG) {
@@ -408,7 +409,7 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
             read_x2(xn, sb, c4n, i);
             if (c4n == 1) { unpack(rwa, 0, 2 * i); unpack(rwa, 0, 2 * i + 1); }
             if (c4n == 3 && i == 3) {
-                wait_vmcnt<Lay::NAW + Lay::NMC>();  // this wave's W copies of the next stage
+                wait_vmcnt<Lay::NAW + Lay::NMC + Lay::FLY>();  // this wave's W copies of the next stage
                 read_raw(rwa, snext, 0);
                 read_raw(rwb, snext, 1);
             }
@@ -429,20 +430,14 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
         SLOT_END();
     };
 
-    if constexpr (PASS2) {  // W taken as zero: clear both W slabs once, never copy them
-        for (int i = tid; i < 2 * (Lay::WB / 16); i += NT)
-            *(u32x4*)(smem + (i / (Lay::WB / 16)) * Lay::STAGE + Lay::W + 16 * (i % (Lay::WB / 16))) = zero_u32x4();
-        __syncthreads();
-    }
-
-    // ---- prologue: stages 0 and 1 in flight, then sub-step 0 of stage 0
+    // ---- prologue: every stage in flight, then sub-step 0 of stage 0
 #pragma unroll
-    for (int j = 0; j < Lay::COPIES; ++j) copy_j(j, 0, lds0);
+    for (int i = 0; i < Lay::S; ++i)
 #pragma unroll
-    for (int j = 0; j < Lay::COPIES; ++j) copy_j(j, nk > 1 ? BK : 0, lds0 + Lay::STAGE);
-    // stage 0 landed everywhere (stage 1's copies, the last issued, may still
-    // fly: the first K-step's barrier waits for them)
-    stage_barrier<PASS2 ? Lay::COPIES - Lay::NWC : Lay::COPIES>();
+        for (int j = 0; j < Lay::COPIES; ++j) copy_j(j, (i < nk ? i : nk - 1) * BK, lds0 + i * Lay::STAGE);
+    // stage 0 landed everywhere (the later stages' copies may still fly: the
+    // K-steps' barriers wait for them)
+    stage_barrier<Lay::FLY + Lay::COPIES>();
     read_mw(smem);
     read_afr(smem, 0);
     if constexpr (FOLD) {
@@ -470,26 +465,28 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
     // ---- main loop (no data-dependent branches: at the tail the copies
     // repeat the last K-slab into the buffer just consumed, and the reads of
     // the "next" stage after the last K-step are never used)
-    for (int kt = 0; kt < nk; ++kt) {
-        const int st = kt & 1;
+    for (int kt = 0, st = 0; kt < nk; ++kt) {
+        constexpr int S = Lay::S;
+        const int sx = st + 1 < S ? st + 1 : 0;  // buffers of K-steps kt+1 and kt-1
+        const int sp = st > 0 ? st - 1 : S - 1;
         const uint8_t* sb = smem + st * Lay::STAGE;
-        const uint8_t* sn = smem + (st ^ 1) * Lay::STAGE;
-        // copies EARLY.. of stage kt+1 (buffer st^1, free since the last
-        // barrier; the barrier below waits for them); at kt = 0 the prologue
-        // issued all of stage 1
-        const int k1 = (kt + 1 < nk ? kt + 1 : nk - 1) * BK;
+        const uint8_t* sn = smem + sx * Lay::STAGE;
+        // copies EARLY.. of stage kt+S-1 (buffer sp, free since the last
+        // barrier); at kt = 0 the prologue issued all of them
+        const int k1 = (kt + S - 1 < nk ? kt + S - 1 : nk - 1) * BK;
         if constexpr (FOLD) {
-            substep_fold(xa, wa, xb, wb, sb, sn, 1, k1, lds0 + (st ^ 1) * Lay::STAGE, kt > 0);
+            substep_fold(xa, wa, xb, wb, sb, sn, 1, k1, lds0 + sp * Lay::STAGE, kt > 0);
             substep_fold(xb, wb, xa, wa, sb, sn, 2);
             substep_fold(xa, wa, xb, wb, sb, sn, 3);
         } else {
-            substep(xa, wa, xb, wb, sb, 1, std::true_type{}, k1, lds0 + (st ^ 1) * Lay::STAGE, kt > 0);
+            substep(xa, wa, xb, wb, sb, 1, std::true_type{}, k1, lds0 + sp * Lay::STAGE, kt > 0);
             substep(xb, wb, xa, wa, sb, 2, std::false_type{});
             substep(xa, wa, xb, wb, sb, 3, std::false_type{});
         }
         // sub-step 3: stage kt+1 landed everywhere, stage kt free
-        stage_barrier<0>();
-        const int k2 = (kt + 2 < nk ? kt + 2 : nk - 1) * BK;
+        // (the FLY copies issued last belong to later stages)
+        stage_barrier<Lay::FLY>();
+        const int k2 = (kt + S < nk ? kt + S : nk - 1) * BK;
         const uint32_t sq = lds0 + st * Lay::STAGE;
         // one copy per MFMA slot: a copy issued behind an MFMA stalls the
         // wave while that MFMA runs, a second one would stall the next
@@ -519,6 +516,7 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
         }
         mm(15, xb, wb);
         SLOT_END();
+        st = sx;
     }
     // ---- epilogue: (+bias), round to bf16, stage the wave's TM x 32 NF block
     // in LDS (rows of 32 NF outputs), then 16-byte stores of whole rows.
@@ -557,12 +555,7 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
         const u32x4 v = *(const u32x4*)(ol + row * OW + 8 * ch);
         const int64_t gm = m0 + row;
         const int gn = n0 + OW * wave + 8 * ch;
-        if (gm < L && gn < R) {
-            if constexpr (PASS2)
-                *(u32x4*)(Y + gm * R + gn) = add_bf16x8(*(const u32x4*)(Y + gm * R + gn), v);
-            else
-                *(u32x4*)(Y + gm * R + gn) = v;
-        }
+        if (gm < L && gn < R) *(u32x4*)(Y + gm * R + gn) = v;
     }
 }
 
@@ -576,30 +569,30 @@ bool power_of_two(float s) {
 
 #ifndef LORS_THIN_TILES
 
-template <int RK, bool TWO_FOUR, bool KRAG, bool PASS2, bool FOLD>
-void launch_whole(const LayerArgs& a, hipStream_t st, int ldb, int grid, int tiles_m, int tiles_n, int n_full,
+template <int RK, bool KRAG, bool FOLD>
+void launch_whole(const LayerArgs& a, hipStream_t st, int grid, int tiles_m, int tiles_n, int n_full,
                   int split, float* part) {
-    hipLaunchKernelGGL((fwd_kernel<RK, TWO_FOUR, KRAG, PASS2, FOLD, BM, 2>), dim3(grid), dim3(NT), 0, st,
+    hipLaunchKernelGGL((fwd_kernel<RK, KRAG, FOLD, BM, 2>), dim3(grid), dim3(NT), 0, st,
                        (const uint16_t*)a.X, (const uint16_t*)a.W, a.M, (const uint16_t*)a.B,
                        (const uint16_t*)a.A, (const uint16_t*)a.bias, (uint16_t*)a.Y, a.L, (int)a.R, (int)a.C,
-                       (int)a.r, a.scale, tiles_m, tiles_n, ldb, n_full, split, part);
+                       (int)a.r, a.scale, tiles_m, tiles_n, n_full, split, part, (int)a.two_four);
 }
 
-template <int RK, bool TWO_FOUR, bool PASS2>
-hipError_t launch_fmt(const LayerArgs& a, hipStream_t st, int ldb) {
+template <int RK>
+hipError_t launch_rk(const LayerArgs& a, hipStream_t st) {
+    if (a.two_four && a.sparse_mfma) return launch_fwd24_bf16(a, st);  // structured-sparse MFMA
     const int tiles_m = (int)((a.L + BM - 1) / BM);
     const int tiles_n = (int)((a.R + BN - 1) / BN);
     const int tiles = tiles_m * tiles_n;
     const bool krag = !fwd_fixed_copies(a.C);
     const bool fold = !krag && power_of_two(a.scale);  // fixed-offset copies with a power-of-two scale
     // A short last wave is cut over K when the caller gave room for the
-    // pieces' partial sums (shapes without whole tiles, one pass only: ranks
-    // up to 64); otherwise it runs as thin tiles (the same bits as whole
+    // pieces' partial sums (shapes without whole tiles); otherwise it runs as thin tiles (the same bits as whole
     // ones, no workspace).
     TailSplit sp{tiles, 1, tiles};
-    if (a.split_ws != nullptr && !PASS2 && a.r <= 64 && !fwd_whole_tiles(a.L, a.R, a.C))
+    if (a.split_ws != nullptr && !fwd_whole_tiles(a.L, a.R, a.C))
         sp = tail_split(tiles, (a.C + BK - 1) / BK, a.split_budget);
-    const ThinPlan tp = (sp.split == 1 && !PASS2) ? thin_plan(tiles) : ThinPlan{tiles, 0, 1};
+    const ThinPlan tp = sp.split == 1 ? thin_plan(tiles) : ThinPlan{tiles, 0, 1};
     float* part = sp.split > 1 ? (float*)a.split_ws : nullptr;
     // with thin tiles the whole-tile grid is exactly the first n_full tiles
     // (work_coords regroups ids over the tiles it is told the grid holds)
@@ -607,75 +600,55 @@ hipError_t launch_fmt(const LayerArgs& a, hipStream_t st, int ldb) {
     const int n_full = tp.q > 1 ? tp.n_full : sp.n_full;
     if (grid > 0) {
         if (krag)
-            launch_whole<RK, TWO_FOUR, true, PASS2, false>(a, st, ldb, grid, tiles_m, tiles_n, n_full, sp.split,
+            launch_whole<RK, true, false>(a, st, grid, tiles_m, tiles_n, n_full, sp.split,
                                                            part);
         else if (fold)
-            launch_whole<RK, TWO_FOUR, false, PASS2, true>(a, st, ldb, grid, tiles_m, tiles_n, n_full, sp.split,
+            launch_whole<RK, false, true>(a, st, grid, tiles_m, tiles_n, n_full, sp.split,
                                                            part);
         else
-            launch_whole<RK, TWO_FOUR, false, PASS2, false>(a, st, ldb, grid, tiles_m, tiles_n, n_full, sp.split,
+            launch_whole<RK, false, false>(a, st, grid, tiles_m, tiles_n, n_full, sp.split,
                                                             part);
     }
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && tp.q > 1) e = launch_fwd_thin_bf16(a, st, ldb, tp.n_full, tp.tail, tp.q);
+    if (e == hipSuccess && tp.q > 1) e = launch_fwd_thin_bf16(a, st, tp.n_full, tp.tail, tp.q);
     if (e == hipSuccess && sp.split > 1)
         e = launch_split_reduce_bf16(part, sp.n_full, sp.split, tiles_m, tiles_n, GROUP_M, a.L, (int)a.R, a.bias,
                                      a.Y, st);
     return e;
 }
 
-template <int RK>
-hipError_t launch_rk(const LayerArgs& a, hipStream_t st, bool pass2, int ldb) {
-    if (a.two_four && a.sparse_mfma) return launch_fwd24_bf16(a, st);  // structured-sparse MFMA
-    if (pass2) return a.two_four ? launch_fmt<RK, true, true>(a, st, ldb) : launch_fmt<RK, false, true>(a, st, ldb);
-    return a.two_four ? launch_fmt<RK, true, false>(a, st, ldb) : launch_fmt<RK, false, false>(a, st, ldb);
-}
-
-hipError_t launch_ranks(const LayerArgs& a, hipStream_t st, bool pass2, int ldb) {
-    switch ((a.r + 15) / 16) {
-        case 1: return launch_rk<1>(a, st, pass2, ldb);
-        case 2: return launch_rk<2>(a, st, pass2, ldb);
-        case 3: return launch_rk<3>(a, st, pass2, ldb);
-        case 4: return launch_rk<4>(a, st, pass2, ldb);
-        default: return hipErrorInvalidValue;
-    }
-}
-
 #else  // LORS_THIN_TILES
 
 // thin tiles of one feature half (NF = 1) and TM tokens: 2 BM / TM per tile
-template <int RK, bool TWO_FOUR, bool KRAG, bool FOLD, int TM>
-hipError_t launch_thin_tm(const LayerArgs& a, hipStream_t st, int ldb, int first, int tail) {
+template <int RK, bool KRAG, bool FOLD, int TM>
+hipError_t launch_thin_tm(const LayerArgs& a, hipStream_t st, int first, int tail) {
     const int tiles_m = (int)((a.L + BM - 1) / BM);
     const int tiles_n = (int)((a.R + BN - 1) / BN);
-    hipLaunchKernelGGL((fwd_kernel<RK, TWO_FOUR, KRAG, false, FOLD, TM, 1>), dim3(tail * (2 * BM / TM)), dim3(NT), 0, st,
+    hipLaunchKernelGGL((fwd_kernel<RK, KRAG, FOLD, TM, 1>), dim3(tail * (2 * BM / TM)), dim3(NT), 0, st,
                        (const uint16_t*)a.X, (const uint16_t*)a.W, a.M, (const uint16_t*)a.B,
                        (const uint16_t*)a.A, (const uint16_t*)a.bias, (uint16_t*)a.Y, a.L, (int)a.R, (int)a.C,
-                       (int)a.r, a.scale, tiles_m, tiles_n, ldb, first, tail, (float*)nullptr);
+                       (int)a.r, a.scale, tiles_m, tiles_n, first, tail, (float*)nullptr,
+                       (int)a.two_four);
     return hipGetLastError();
 }
 
-template <int RK, bool TWO_FOUR, bool KRAG, bool FOLD>
-hipError_t launch_thin_q(const LayerArgs& a, hipStream_t st, int ldb, int first, int tail, int q) {
+template <int RK, bool KRAG, bool FOLD>
+hipError_t launch_thin_q(const LayerArgs& a, hipStream_t st, int first, int tail, int q) {
     switch (q) {  // q thin tiles per tile: two feature halves, each cut into q/2 token parts
-        case 2: return launch_thin_tm<RK, TWO_FOUR, KRAG, FOLD, BM>(a, st, ldb, first, tail);
-        case 4: return launch_thin_tm<RK, TWO_FOUR, KRAG, FOLD, BM / 2>(a, st, ldb, first, tail);
-        case 8: return launch_thin_tm<RK, TWO_FOUR, KRAG, FOLD, BM / 4>(a, st, ldb, first, tail);
+        case 2: return launch_thin_tm<RK, KRAG, FOLD, BM>(a, st, first, tail);
+        case 4: return launch_thin_tm<RK, KRAG, FOLD, BM / 2>(a, st, first, tail);
+        case 8: return launch_thin_tm<RK, KRAG, FOLD, BM / 4>(a, st, first, tail);
         default: return hipErrorInvalidValue;
     }
 }
 
 template <int RK>
-hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int ldb, int first, int tail, int q) {
+hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int first, int tail, int q) {
     const bool krag = !fwd_fixed_copies(a.C);
     const bool fold = !krag && power_of_two(a.scale);
-    if (a.two_four)
-        return krag   ? launch_thin_q<RK, true, true, false>(a, st, ldb, first, tail, q)
-               : fold ? launch_thin_q<RK, true, false, true>(a, st, ldb, first, tail, q)
-                      : launch_thin_q<RK, true, false, false>(a, st, ldb, first, tail, q);
-    return krag   ? launch_thin_q<RK, false, true, false>(a, st, ldb, first, tail, q)
-           : fold ? launch_thin_q<RK, false, false, true>(a, st, ldb, first, tail, q)
-                  : launch_thin_q<RK, false, false, false>(a, st, ldb, first, tail, q);
+    return krag   ? launch_thin_q<RK, true, false>(a, st, first, tail, q)
+           : fold ? launch_thin_q<RK, false, true>(a, st, first, tail, q)
+                  : launch_thin_q<RK, false, false>(a, st, first, tail, q);
 }
 
 #endif  // LORS_THIN_TILES
@@ -686,35 +659,40 @@ hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int ldb, int first
 
 hipError_t launch_fwd_bf16(const LayerArgs& a, hipStream_t st) {
     if (a.L == 0) return hipSuccess;
-    if (a.r <= 64) return launch_ranks(a, st, false, (int)a.r);
+    switch ((a.r + 15) / 16) {
+        case 1: return launch_rk<1>(a, st);
+        case 2: return launch_rk<2>(a, st);
+        case 3: return launch_rk<3>(a, st);
+        case 4: return launch_rk<4>(a, st);
+        default: break;
+    }
     if (a.r > 128) return hipErrorInvalidValue;  // the problem check caps r at 128
-    // Ranks above 64: the mask distributes over the sum, so
-    //   W' = select(M, W + s.B1.A1, 0) + select(M, s.B2.A2, 0)
-    // for ranks [0, 64) and [64, r): two passes of the register-merge
-    // kernel, the second with W taken as zero, no bias, and its product added
-    // onto Y (one more bf16 rounding of Y).
-    LayerArgs a1 = a;
-    a1.r = 64;
-    const hipError_t e = launch_ranks(a1, st, false, (int)a.r);
-    if (e != hipSuccess) return e;
-    LayerArgs a2 = a;
-    a2.r = a.r - 64;
-    a2.B = (const uint16_t*)a.B + 64;
-    a2.A = (const uint16_t*)a.A + 64 * a.C;
-    a2.bias = nullptr;
-    return launch_ranks(a2, st, true, (int)a.r);
+    // Ranks above 64: a wave has registers for the rank-r operands of one
+    // 32-feature block only, so every tile runs as half-feature thin tiles.
+    // One pass: 104 us at 4096 x 4096, 2048 tokens, rank 128, against 211 us
+    // for two passes of whole tiles over the ranks below and above 64, the
+    // second adding onto Y (dX: 107 against 211).
+    int first[2], tail[2], q[2];
+    const int64_t tiles = ((a.L + BM - 1) / BM) * ((a.R + BN - 1) / BN);
+    const int n = thin_only_plan(tiles, first, tail, q);
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < n && e == hipSuccess; ++i) e = launch_fwd_thin_bf16(a, st, first[i], tail[i], q[i]);
+    return e;
 }
 
 #else
 
-hipError_t launch_fwd_thin_bf16(const LayerArgs& a, hipStream_t st, int ldb, int first, int tail, int q) {
+hipError_t launch_fwd_thin_bf16(const LayerArgs& a, hipStream_t st, int first, int tail, int q) {
     if (tail <= 0) return hipSuccess;
-    if (a.r < 1 || a.r > 64) return hipErrorInvalidValue;
     switch ((a.r + 15) / 16) {
-        case 1: return launch_thin_rk<1>(a, st, ldb, first, tail, q);
-        case 2: return launch_thin_rk<2>(a, st, ldb, first, tail, q);
-        case 3: return launch_thin_rk<3>(a, st, ldb, first, tail, q);
-        case 4: return launch_thin_rk<4>(a, st, ldb, first, tail, q);
+        case 1: return launch_thin_rk<1>(a, st, first, tail, q);
+        case 2: return launch_thin_rk<2>(a, st, first, tail, q);
+        case 3: return launch_thin_rk<3>(a, st, first, tail, q);
+        case 4: return launch_thin_rk<4>(a, st, first, tail, q);
+        case 5: return launch_thin_rk<5>(a, st, first, tail, q);
+        case 6: return launch_thin_rk<6>(a, st, first, tail, q);
+        case 7: return launch_thin_rk<7>(a, st, first, tail, q);
+        case 8: return launch_thin_rk<8>(a, st, first, tail, q);
         default: return hipErrorInvalidValue;
     }
 }

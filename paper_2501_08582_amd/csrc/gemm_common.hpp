@@ -34,6 +34,16 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
 
+// LDS stages of a main loop: a short K-step (a thin tile's) is over before its
+// successor's copies return from memory, so two stages leave it waiting; up to
+// four are taken where they fit beside `extra` bytes.  (128-token thin tiles of
+// 5120 x 5120, 4096 tokens, rank 64: 88 us with two stages, 84 with three; a
+// K-step of a whole tile covers the copies' return, and its stages fill LDS.)
+constexpr int kLdsBytes = 160 * 1024;
+constexpr int stages_that_fit(int stage, int extra) {
+    return 4 * stage + extra <= kLdsBytes ? 4 : 3 * stage + extra <= kLdsBytes ? 3 : 2;
+}
+
 // One 16-byte global -> LDS copy per lane (global_load_lds_dwordx4): lane l's
 // data lands at LDS byte address lds_wave_base + 16*l; lds_wave_base must be
 // wave-uniform.  Issued as inline assembly so that the compiler does not
@@ -176,28 +186,22 @@ __device__ __forceinline__ void copy4s_to_lds(const void* sbase, uint32_t voff, 
 template <int RK, int NB>
 __device__ __forceinline__ void rank_wait(f32x16 (&T)[NB], const bf16x8 (&a)[RK]) {
     static_assert(NB == 1 || NB == 2, "one or two 32-wide blocks");
-    static_assert(RK >= 1 && RK <= 4, "ranks up to 64");
-    if constexpr (NB == 2) {
-        if constexpr (RK == 1)
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2" : "+v"(T[0]), "+v"(T[1]) : "v"(a[0]));
-        else if constexpr (RK == 2)
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2" : "+v"(T[0]), "+v"(T[1]) : "v"(a[0]), "v"(a[1]));
-        else if constexpr (RK == 3)
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2" : "+v"(T[0]), "+v"(T[1]) : "v"(a[0]), "v"(a[1]), "v"(a[2]));
-        else
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2"
-                         : "+v"(T[0]), "+v"(T[1])
-                         : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]));
-    } else {
-        if constexpr (RK == 1)
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2" : "+v"(T[0]) : "v"(a[0]));
-        else if constexpr (RK == 2)
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2" : "+v"(T[0]) : "v"(a[0]), "v"(a[1]));
-        else if constexpr (RK == 3)
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2" : "+v"(T[0]) : "v"(a[0]), "v"(a[1]), "v"(a[2]));
-        else
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2" : "+v"(T[0]) : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]));
-    }
+    static_assert(RK >= 1 && RK <= (NB == 1 ? 8 : 4), "ranks up to 128, or 64 for two blocks");
+    // (an operand past RK repeats the last fragment)
+    constexpr auto at = [](int c) { return c < RK ? c : RK - 1; };
+    if constexpr (NB == 2 && RK <= 4)
+        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2"
+                     : "+v"(T[0]), "+v"(T[1])
+                     : "v"(a[0]), "v"(a[at(1)]), "v"(a[at(2)]), "v"(a[at(3)]));
+    else if constexpr (RK <= 4)
+        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2"
+                     : "+v"(T[0])
+                     : "v"(a[0]), "v"(a[at(1)]), "v"(a[at(2)]), "v"(a[at(3)]));
+    else
+        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2"
+                     : "+v"(T[0])
+                     : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[at(5)]), "v"(a[at(6)]),
+                       "v"(a[at(7)]));
 }
 
 // T[nb] = sum over c of mfma(a[c], b[nb][c]) for nb < NB (two 32-wide blocks,

@@ -67,6 +67,11 @@ struct ThinPlan {
     int n_full, tail, q;
 };
 ThinPlan thin_plan(int64_t tiles);
+// A grid of thin tiles only: the tiles' runs [first, first + tail) and the q
+// of each, one launch per run (at most two, the count is returned).  Whole
+// waves run as feature halves (q = 2); a short last wave, or a grid that is
+// one, takes the larger q of thin_plan's rule.
+int thin_only_plan(int64_t tiles, int first[2], int tail[2], int q[2]);
 // Shapes of whole tiles, which never split over K: 256 x 256 tiles and 64-wide
 // K-steps cover the forward's L x R, K = C (dX's L x C, K = R) exactly.
 inline bool fwd_whole_tiles(int64_t L, int64_t R, int64_t C) {
@@ -93,12 +98,11 @@ hipError_t launch_split_reduce_bf16(const float* part, int n_full, int split, in
 hipError_t launch_fwd_bf16(const LayerArgs& a, hipStream_t s);
 hipError_t launch_fwd24_bf16(const LayerArgs& a, hipStream_t s);      // 2:4 mask, sparse MFMA, rank <= 64
 hipError_t launch_dx_bf16(const LayerArgs& a, hipStream_t s);
-// The thin tiles of a short last wave (see ThinPlan): logical tiles first ..
-// first+tail-1, each cut into q; single-pass ranks (a.r <= 64).  ldb: row stride of B; ra: rows of A that exist; clear: the launch
-// also clears dB and dA (it is the first of the dX launches).
-hipError_t launch_fwd_thin_bf16(const LayerArgs& a, hipStream_t s, int ldb, int first, int tail, int q);
-hipError_t launch_dx_thin_bf16(const LayerArgs& a, hipStream_t s, int ldb, int ra, int first, int tail, int q,
-                               bool clear);
+// Thin tiles (see ThinPlan): logical tiles first .. first+tail-1, each cut
+// into q.  ra: rows of A that exist; clear: the launch also clears dB and dA
+// (it is the first of the dX launches).
+hipError_t launch_fwd_thin_bf16(const LayerArgs& a, hipStream_t s, int first, int tail, int q);
+hipError_t launch_dx_thin_bf16(const LayerArgs& a, hipStream_t s, int ra, int first, int tail, int q, bool clear);
 hipError_t launch_g_bf16(const LayerArgs& a, hipStream_t s);
 hipError_t launch_ste_bf16(const LayerArgs& a, hipStream_t s);  // dB, dA of the straight-through backward
 size_t ste_workspace_bytes(int64_t R, int64_t L, int64_t r);

@@ -356,6 +356,19 @@ ThinPlan thin_plan(int64_t tiles) {
     return t;
 }
 
+int thin_only_plan(int64_t tiles, int first[2], int tail[2], int q[2]) {
+    const int cus = device_cus();
+    const int64_t rest = (2 * tiles % cus + 1) / 2;  // tiles of the last wave of feature halves
+    const int whole = (int)(4 * rest <= cus ? tiles - rest : tiles);
+    int n = 0;
+    if (whole > 0) { first[n] = 0; tail[n] = whole; q[n++] = 2; }
+    if (whole < tiles) {
+        const int t = (int)(tiles - whole);
+        first[n] = whole; tail[n] = t; q[n++] = 8 * t <= cus ? 8 : 4;
+    }
+    return n;
+}
+
 hipError_t launch_zero2_f32(float* a, int64_t na, float* b, int64_t nb, hipStream_t st) {
     const int64_t n = na + nb;
     if (n == 0) return hipSuccess;

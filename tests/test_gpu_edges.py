@@ -39,7 +39,9 @@ def _guarded(shape, dtype):
     (192, 264, 321, 64, "magnitude", 1.5),    # forward: checked copies, thin
     (1032, 1096, 130, 24, "2:4", 2.0),        # both, odd feature halves
     (4160, 4224, 513, 16, "magnitude", 2.0),  # three token tiles, the last of one token
-    (256, 256, 300, 100, "magnitude", 2.0),   # ranks above 64
+    (256, 256, 300, 100, "magnitude", 2.0),   # ranks above 64: feature halves, no whole wave
+    (264, 328, 193, 72, "2:4", 0.3),
+    (320, 4160, 2300, 128, "magnitude", 1.0), # dX: a wave of feature halves, then thinner tiles
 ])
 def test_edges(R, C, L, r, mask, scale):
     name = "llama2_7b_up_proj_2_4" if mask == "2:4" else "llama2_7b_q_proj"
