@@ -96,6 +96,7 @@ hipError_t launch_split_reduce_bf16(const float* part, int n_full, int split, in
 
 // bf16 path
 hipError_t launch_fwd_bf16(const LayerArgs& a, hipStream_t s);
+hipError_t launch_fwd_few_bf16(const LayerArgs& a, hipStream_t s);  // few tokens
 hipError_t launch_fwd24_bf16(const LayerArgs& a, hipStream_t s);      // 2:4 mask, sparse MFMA, rank <= 64
 hipError_t launch_dx_bf16(const LayerArgs& a, hipStream_t s);
 // Thin tiles (see ThinPlan): logical tiles first .. first+tail-1, each cut

@@ -66,3 +66,40 @@ def test_edges(R, C, L, r, mask, scale):
         assert np.all(np.isfinite(got)), f"{k}: not finite"
         err, at = worst_tile(got, want[k], (64, 64))
         assert err <= TOL["bf16"], f"{k} block {at}: rel err {err:.3e}"
+
+
+# the kernel for few tokens: 16- and 32-feature workgroups, each token block,
+# each rank bucket, contractions below, at and past one block per wave, with
+# and without a ragged last block; the last row of a case is past the rule
+# (its 65 tokens run as thin tiles)
+@pytest.mark.parametrize("R,C,L,r,mask,scale", [
+    (8, 8, 1, 1, "magnitude", 2.0),
+    (40, 64, 16, 16, "2:4", 0.5),
+    (4096, 1024, 17, 32, "magnitude", 1.5),
+    (264, 2120, 33, 48, "2:4", 2.0),
+    (1024, 584, 64, 64, "magnitude", 2.0),
+    (520, 1096, 65, 90, "2:4", 0.1),
+    (256, 1096, 130, 128, "magnitude", 2.0),
+    (8200, 328, 9, 12, "2:4", 2.0),
+    (8232, 640, 31, 64, "magnitude", 1.0),
+    (8192, 72, 32, 128, "magnitude", 2.0),
+    (8192, 192, 65, 16, "magnitude", 2.0),
+])
+def test_few_tokens_forward(R, C, L, r, mask, scale):
+    name = "llama2_7b_up_proj_2_4" if mask == "2:4" else "llama2_7b_q_proj"
+    inp = synth.make(synth.workload(name).with_(R=R, C=C, r=r, scale=scale, seed=5000 + R + L), L=L)
+    inp.W = unprune(inp.W, inp.M, "bf16", seed=L)
+    bias = synth.f32_to_bf16_bits(np.random.default_rng(L).standard_normal(R).astype(np.float32) * 0.1)
+    X, W, B, A, bt = (to_dev(t, "bf16") for t in (inp.X, inp.W, inp.B, inp.A, bias))
+    M = ops.mask_pack(torch.from_numpy(inp.M).cuda(), FMT[mask])
+    print("few tokens", (R, C, L, r, mask, scale), flush=True)
+    buf, Y = _guarded((L, R), torch.bfloat16)
+    ops.forward(X, W, M, B, A, scale, FMT[mask], bias=bt, out=Y)
+    again = ops.forward(X, W, M, B, A, scale, FMT[mask], bias=bt)
+    torch.cuda.synchronize()
+    n = Y.numel() * 2
+    assert torch.all(buf[:GUARD] == 0xA5) and torch.all(buf[GUARD + n:] == 0xA5), "a guard byte changed"
+    assert torch.equal(Y, again)  # the waves' partial sums are added in a fixed order
+    x, w, b, a = (to_f64(t, "bf16") for t in (inp.X, inp.W, inp.B, inp.A))
+    err, at = worst_tile(dev_to_f64(Y), olors.forward(x, w, inp.M, b, a, scale, to_f64(bias, "bf16")), (32, 32))
+    assert err <= TOL["bf16"], f"block {at}: rel err {err:.3e}"
