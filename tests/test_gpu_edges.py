@@ -103,3 +103,66 @@ def test_few_tokens_forward(R, C, L, r, mask, scale):
     x, w, b, a = (to_f64(t, "bf16") for t in (inp.X, inp.W, inp.B, inp.A))
     err, at = worst_tile(dev_to_f64(Y), olors.forward(x, w, inp.M, b, a, scale, to_f64(bias, "bf16")), (32, 32))
     assert err <= TOL["bf16"], f"block {at}: rel err {err:.3e}"
+
+
+def test_two_four_rows_past_the_output_features_are_dropped():
+    """R is no multiple of 32: the weight gradient's tile has rows past R,
+    computed from repeated columns of dY.  An infinity in the last column of
+    dY may reach dA only where the last row's mask keeps an entry."""
+    R, C, L, r = 264, 256, 128, 16
+    inp = synth.make(synth.workload("llama2_7b_up_proj_2_4").with_(R=R, C=C, r=r, seed=6000), L=L)
+    X, W, B, A, dY = (to_dev(t, "bf16") for t in (inp.X, inp.W, inp.B, inp.A, inp.dY))
+    dY[5, R - 1] = float("inf")
+    M = ops.mask_pack(torch.from_numpy(inp.M).cuda(), ops.TWO_FOUR)
+    dA = ops.backward(dY, X, W, M, B, A, 2.0, ops.TWO_FOUR, need_dx=False)[2]
+    dropped = torch.from_numpy(inp.M[R - 1] == 0).cuda()
+    assert torch.isfinite(dA[:, dropped]).all()
+    assert not torch.isfinite(dA[:, ~dropped]).any()
+
+
+# fp32: 32 x 32 tiles and 32-wide k blocks, each rank-pair bucket, more blocks
+# than waves; sums of up to 600 products in another order stay within 1e-5
+@pytest.mark.parametrize("R,C,L,r,mask,scale", [
+    (4, 4, 1, 1, "random", 2.0), (32, 36, 31, 8, "2:4", 1.5), (100, 300, 33, 9, "random", 0.3),
+    (36, 600, 97, 32, "2:4", 2.0), (132, 68, 300, 64, "random", 1.0), (68, 132, 65, 101, "2:4", 0.5),
+])
+def test_fp32_edges(R, C, L, r, mask, scale):
+    wl = synth.workload("fp32_256x256_r8").with_(R=R, C=C, r=r, mask=mask, scale=scale, seed=7000 + R)
+    inp = synth.make(wl, L=L)
+    inp.W = unprune(inp.W, inp.M, "f32", seed=R)
+    fmt = ops.TWO_FOUR if mask == "2:4" else ops.BITMAP
+    X, W, B, A, dY = (to_dev(t, "f32") for t in (inp.X, inp.W, inp.B, inp.A, inp.dY))
+    M = ops.mask_pack(torch.from_numpy(inp.M).cuda(), fmt)
+    bias = np.random.default_rng(R).standard_normal(R).astype(np.float32)
+    Y = ops.forward(X, W, M, B, A, scale, fmt, bias=to_dev(bias, "f32"))
+    dX, dB, dA, dbias = ops.backward(dY, X, W, M, B, A, scale, fmt, need_dbias=True)
+    x, w, b, a, dy = (np.asarray(t, np.float64) for t in (inp.X, inp.W, inp.B, inp.A, inp.dY))
+    ref = olors.backward(dy, x, w, inp.M, b, a, scale, with_bias=True)
+    for k, got, want in zip(("Y", "dX", "dB", "dA", "dbias"), (Y, dX, dB, dA, dbias),
+                            (olors.forward(x, w, inp.M, b, a, scale, np.asarray(bias, np.float64)), *ref)):
+        err, at = worst_tile(dev_to_f64(got), want, (32, 32))
+        assert err <= TOL["f32"], f"{k} block {at}: rel err {err:.3e}"
+
+
+# mask derivation and packing: whole-word rows (vector loads, a last wave of
+# words that is not full) and rows that end inside a word
+@pytest.mark.parametrize("dtype", [torch.uint8, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("R,C,fmt", [(1, 32, ops.BITMAP), (3, 352, ops.TWO_FOUR), (67, 96, ops.BITMAP),
+                                     (65, 1024, ops.TWO_FOUR), (5, 36, ops.TWO_FOUR), (9, 1000, ops.BITMAP)])
+def test_mask_words(dtype, R, C, fmt):
+    from oracle import masks as omasks
+    rng = np.random.default_rng(R + C)
+    keep = rng.random((R, C)) < 0.5
+    if fmt == ops.TWO_FOUR:
+        keep = (rng.random((R, C // 4, 4)).argsort(2) < 2).reshape(R, C)
+    val = torch.from_numpy(rng.integers(1, 200, (R, C))).to(dtype) * torch.from_numpy(keep).to(dtype)
+    if dtype != torch.uint8:
+        val = torch.where(torch.from_numpy(rng.random((R, C)) < 0.5), -val, val)  # -0 counts as zero
+    M = ops.mask_pack(val.cuda(), fmt) if dtype == torch.uint8 else ops.mask_from_weight(val.cuda(), fmt)
+    pack = omasks.pack_2_4 if fmt == ops.TWO_FOUR else omasks.pack_bitmap
+    assert np.array_equal(M.cpu().numpy().view(np.uint32).reshape(-1), np.asarray(pack(keep.astype(np.uint8))).reshape(-1))
+    if fmt == ops.TWO_FOUR:  # the first bad group, wherever it lies
+        g = int(rng.integers(R * (C // 4)))
+        val.view(R * C // 4, 4)[g] = 0
+        with pytest.raises(ValueError, match=f"row {g // (C // 4)}, group {g % (C // 4)}"):
+            ops.mask_pack(val.cuda(), fmt) if dtype == torch.uint8 else ops.mask_from_weight(val.cuda(), fmt)
