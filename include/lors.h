@@ -317,6 +317,17 @@ lors_status_t lors_backward_noalloc(const lors_problem_t* p, const void* dY,
                                     const void* A, void* dX, float* dB,
                                     float* dA, float* dbias, void* stream);
 
+/*
+ * Two fp32 arrays (dB and dA) rounded to bf16, nearest-even, with one launch:
+ * a_out[i] = bf16(a[i]) for i < na, b_out[i] = bf16(b[i]) for i < nb, for a
+ * caller whose adapters are bf16.  A pointer may be NULL when its count is 0.
+ * LORS_ERR_SHAPE for a count below 0 or of more than 2^58; pointers are 16-byte
+ * aligned; no output may overlap an input or the other output.  Asynchronous.
+ */
+lors_status_t lors_round_bf16(const float* a, int64_t na, void* a_out,
+                              const float* b, int64_t nb, void* b_out,
+                              void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -39,7 +39,7 @@ EXPORTED = (
     "lors_status_string", "lors_version", "lors_mask_packed_bytes", "lors_mask_pack",
     "lors_mask_unpack", "lors_mask_from_weight", "lors_mask_pack_host", "lors_mask_unpack_host",
     "lors_workspace_bytes", "lors_forward", "lors_backward", "lors_backward_data",
-    "lors_backward_weight", "lors_backward_noalloc",
+    "lors_backward_weight", "lors_backward_noalloc", "lors_round_bf16",
 )
 NOALLOC_SCRATCH_BYTES = 32 << 20
 
@@ -90,6 +90,7 @@ def _declare(lib) -> None:
         "lors_backward_data": (ctypes.c_int, [P, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
         "lors_backward_weight": (ctypes.c_int,
                                  [P, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
+        "lors_round_bf16": (ctypes.c_int, [_vp, _i64, _vp, _vp, _i64, _vp, _vp]),
         "lors_backward_noalloc": (ctypes.c_int, [P, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]),
     }
     for name, (res, args) in sig.items():
@@ -177,3 +178,7 @@ def backward_weight(p: Problem, dY, X, M, B, A, dB, dA, dbias, ws, ws_bytes, str
 
 def backward_noalloc(p: Problem, dY, X, W, M, B, A, dX, dB, dA, dbias, stream) -> int:
     return lib().lors_backward_noalloc(ctypes.byref(p), dY, X, W, M, B, A, dX, dB, dA, dbias, stream)
+
+
+def round_bf16(a, na, a_out, b, nb, b_out, stream) -> int:
+    return lib().lors_round_bf16(a, int(na), a_out, b, int(nb), b_out, stream)

@@ -477,6 +477,21 @@ lors_status_t lors_backward_weight(const lors_problem_t* p, const void* dY, cons
     return from_hip(e);
 }
 
+lors_status_t lors_round_bf16(const float* a, int64_t na, void* a_out, const float* b, int64_t nb, void* b_out,
+                              void* stream) {
+    if ((na != 0 && (a == nullptr || a_out == nullptr)) || (nb != 0 && (b == nullptr || b_out == nullptr)))
+        return LORS_ERR_NULL;
+    if (bytes_of(na, 1, 4) < 0 || bytes_of(nb, 1, 4) < 0) return LORS_ERR_SHAPE;
+    if (!aligned16(a) || !aligned16(a_out) || !aligned16(b) || !aligned16(b_out)) return LORS_ERR_ALIGN;
+    const Range in[] = {range_of(a, 4 * na), range_of(b, 4 * nb)};
+    const Range out[] = {range_of(a_out, 2 * na), range_of(b_out, 2 * nb)};
+    for (const Range& o : out)
+        for (const Range& i : in)
+            if (overlap(o, i)) return LORS_ERR_ALIAS;
+    if (overlap(out[0], out[1])) return LORS_ERR_ALIAS;
+    return from_hip(lors::launch_round_bf16(a, na, a_out, b, nb, b_out, static_cast<hipStream_t>(stream)));
+}
+
 }  // extern "C"
 
 // ---------------------------------------------------------------------------

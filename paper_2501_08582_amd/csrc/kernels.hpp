@@ -121,6 +121,9 @@ hipError_t launch_zero_f32(float* p, int64_t n, hipStream_t s);
 hipError_t launch_pad_cols_bf16(const void* B, int64_t R, int64_t r, int64_t rp, void* out, hipStream_t s);
 // clears two fp32 buffers with one launch
 hipError_t launch_zero2_f32(float* a, int64_t na, float* b, int64_t nb, hipStream_t s);
+// a_out = bf16(a), b_out = bf16(b) with one launch
+hipError_t launch_round_bf16(const float* a, int64_t na, void* a_out, const float* b, int64_t nb, void* b_out,
+                             hipStream_t s);
 hipError_t launch_mask_pack(const uint8_t* dense, int64_t R, int64_t C, bool two_four,
                             uint32_t* packed, int64_t* first_bad, hipStream_t s);
 hipError_t launch_mask_from_weight(const void* W, bool w_is_bf16, int64_t R, int64_t C,

@@ -192,6 +192,25 @@ __global__ __launch_bounds__(NT) void zero2_kernel(float* __restrict__ a, int64_
     }
 }
 
+// The two arrays as runs of 4-element vectors (their last one may be short).
+__global__ __launch_bounds__(NT) void round_bf16_kernel(const float* __restrict__ a, int64_t na,
+                                                        uint16_t* __restrict__ ao, const float* __restrict__ b,
+                                                        int64_t nb, uint16_t* __restrict__ bo) {
+    const int64_t va = (na + 3) / 4, vb = (nb + 3) / 4, stride = (int64_t)gridDim.x * NT;
+    for (int64_t t = (int64_t)blockIdx.x * NT + threadIdx.x; t < va + vb; t += stride) {
+        const bool first = t < va;
+        const int64_t e = 4 * (first ? t : t - va), left = (first ? na : nb) - e;
+        const float* p = (first ? a : b) + e;
+        uint16_t* o = (first ? ao : bo) + e;
+        if (left >= 4) {
+            const f32x4 v = *(const f32x4*)p;
+            *(u32x2*)o = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+        } else {
+            for (int i = 0; i < left; ++i) o[i] = bf16_bits(p[i]);
+        }
+    }
+}
+
 // out[R x rp] = B[R x r] with columns r .. rp-1 zero (bf16 bit patterns).
 __global__ __launch_bounds__(NT) void pad_cols_kernel(const uint16_t* __restrict__ B, int64_t R, int r, int rp,
                                                       uint16_t* __restrict__ out) {
@@ -416,6 +435,17 @@ hipError_t launch_zero2_f32(float* a, int64_t na, float* b, int64_t nb, hipStrea
     const int64_t want = (n + NT - 1) / NT;
     const unsigned blocks = (unsigned)(want < 2048 ? want : 2048);
     hipLaunchKernelGGL(zero2_kernel, dim3(blocks), dim3(NT), 0, st, a, na, b, nb);
+    return hipGetLastError();
+}
+
+hipError_t launch_round_bf16(const float* a, int64_t na, void* a_out, const float* b, int64_t nb, void* b_out,
+                             hipStream_t st) {
+    const int64_t n = (na + 3) / 4 + (nb + 3) / 4;
+    if (n == 0) return hipSuccess;
+    const int64_t want = (n + NT - 1) / NT;
+    const unsigned blocks = (unsigned)(want < 2048 ? want : 2048);
+    hipLaunchKernelGGL(round_bf16_kernel, dim3(blocks), dim3(NT), 0, st, a, na, (uint16_t*)a_out, b, nb,
+                       (uint16_t*)b_out);
     return hipGetLastError();
 }
 

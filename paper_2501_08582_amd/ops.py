@@ -55,7 +55,24 @@ def _dev(*ts: Optional[torch.Tensor]) -> torch.device:
 
 
 def _stream(dev: torch.device) -> int:
-    return torch.cuda.current_stream(dev).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(dev.index)
+
+
+def _call(dev: torch.device, where: str, fn, *args) -> None:
+    """fn(*args, current stream of dev) with dev the current device.  A small
+    layer's calls are bound by the host, so the device is only switched when
+    it differs and the stream is not wrapped in an object (4 us a call)."""
+    if torch.cuda.current_device() == dev.index:
+        status = fn(*args, _stream(dev))
+    else:
+        with torch.cuda.device(dev):
+            status = fn(*args, _stream(dev))
+    _lib.check(status, where)
+
+
+def _rows(X: torch.Tensor) -> torch.Tensor:
+    """X with its leading dimensions flattened to one."""
+    return X if X.dim() == 2 else X.reshape(-1, X.shape[-1])
 
 
 def mask_words(R: int, C: int) -> int:
@@ -73,9 +90,7 @@ def mask_pack(dense: torch.Tensor, mask_format=BITMAP) -> torch.Tensor:
     packed = torch.empty(mask_words(R, C), dtype=torch.int32, device=dev)
     bad = torch.empty(1, dtype=torch.int64, device=dev)
     fmt = _fmt(mask_format)
-    with torch.cuda.device(dev):
-        _lib.check(_lib.mask_pack(_ptr(dense), R, C, fmt, _ptr(packed), _ptr(bad), _stream(dev)),
-                   "lors_mask_pack")
+    _call(dev, "lors_mask_pack", _lib.mask_pack, _ptr(dense), R, C, fmt, _ptr(packed), _ptr(bad))
     if fmt == _lib.MASK_2_4:
         b = int(bad.item())
         if b >= 0:
@@ -90,9 +105,7 @@ def mask_from_weight(W: torch.Tensor, mask_format=BITMAP) -> torch.Tensor:
     packed = torch.empty(mask_words(R, C), dtype=torch.int32, device=dev)
     bad = torch.empty(1, dtype=torch.int64, device=dev)
     fmt = _fmt(mask_format)
-    with torch.cuda.device(dev):
-        _lib.check(_lib.mask_from_weight(_ptr(W), _dt(W), R, C, fmt, _ptr(packed), _ptr(bad),
-                                         _stream(dev)), "lors_mask_from_weight")
+    _call(dev, "lors_mask_from_weight", _lib.mask_from_weight, _ptr(W), _dt(W), R, C, fmt, _ptr(packed), _ptr(bad))
     if fmt == _lib.MASK_2_4:
         b = int(bad.item())
         if b >= 0:
@@ -105,9 +118,7 @@ def mask_unpack(packed: torch.Tensor, R: int, C: int, mask_format=BITMAP) -> tor
     if packed.dtype != torch.int32 or packed.numel() != mask_words(R, C):
         raise ValueError("packed mask must be int32 with R*ceil(C/32) words")
     dense = torch.empty((R, C), dtype=torch.uint8, device=dev)
-    with torch.cuda.device(dev):
-        _lib.check(_lib.mask_unpack(_ptr(packed), R, C, _fmt(mask_format), _ptr(dense), _stream(dev)),
-                   "lors_mask_unpack")
+    _call(dev, "lors_mask_unpack", _lib.mask_unpack, _ptr(packed), R, C, _fmt(mask_format), _ptr(dense))
     return dense
 
 
@@ -126,8 +137,7 @@ def forward(X: torch.Tensor, W: torch.Tensor, M: torch.Tensor, B: torch.Tensor, 
     sparse MFMA instead of the dense one.  ``split_last_wave`` cuts a partial
     last wave of output tiles over K (LORS_FLAG_SPLIT_LAST_WAVE; a workspace
     is allocated here)."""
-    lead = X.shape[:-1]
-    X2 = X.reshape(-1, X.shape[-1])
+    X2 = _rows(X)
     dev = _dev(X2, W, M, B, A, bias)
     R = W.shape[0]
     if out is None:
@@ -136,10 +146,9 @@ def forward(X: torch.Tensor, W: torch.Tensor, M: torch.Tensor, B: torch.Tensor, 
     p = _problem(X2, W, B, mask_format, scale, flags=flags)
     need = _lib.workspace_bytes(p) if split_last_wave else 0
     ws = torch.empty(need, dtype=torch.uint8, device=dev) if need else None
-    with torch.cuda.device(dev):
-        _lib.check(_lib.forward(p, _ptr(X2), _ptr(W), _ptr(M), _ptr(B), _ptr(A), _ptr(bias), _ptr(out),
-                                _ptr(ws), need, _stream(dev)), "lors_forward")
-    return out.view(*lead, R)
+    _call(dev, "lors_forward", _lib.forward, p, _ptr(X2), _ptr(W), _ptr(M), _ptr(B), _ptr(A), _ptr(bias), _ptr(out),
+          _ptr(ws), need)
+    return out if X2 is X and out.dim() == 2 else out.view(*X.shape[:-1], R)
 
 
 def workspace_bytes(W: torch.Tensor, B: torch.Tensor, L: int, mask_format=BITMAP, ste: bool = False) -> int:
@@ -165,8 +174,7 @@ def backward(dY: torch.Tensor, X: torch.Tensor, W: torch.Tensor, M: torch.Tensor
     last wave of dX tiles over K (LORS_FLAG_SPLIT_LAST_WAVE).  ``workspace``
     (uint8, at least what the library reports for the same flags) is
     allocated here when not given."""
-    X2 = X.reshape(-1, X.shape[-1])
-    dY2 = dY.reshape(-1, dY.shape[-1])
+    X2, dY2 = _rows(X), _rows(dY)
     dev = _dev(dY2, X2, W, M, B, A)
     R, C = W.shape
     r = B.shape[1]
@@ -184,12 +192,35 @@ def backward(dY: torch.Tensor, X: torch.Tensor, W: torch.Tensor, M: torch.Tensor
     if workspace is None and need:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     wsb = workspace.numel() if workspace is not None else 0
-    with torch.cuda.device(dev):
-        _lib.check(_lib.backward(p, _ptr(dY2), _ptr(X2), _ptr(W), _ptr(M), _ptr(B), _ptr(A), _ptr(dX),
-                                 _ptr(dB), _ptr(dA), _ptr(dbias), _ptr(workspace), wsb, _stream(dev)),
-                   "lors_backward")
-    if dX is not None:
+    _call(dev, "lors_backward", _lib.backward, p, _ptr(dY2), _ptr(X2), _ptr(W), _ptr(M), _ptr(B), _ptr(A), _ptr(dX),
+          _ptr(dB), _ptr(dA), _ptr(dbias), _ptr(workspace), wsb)
+    if dX is not None and not (X2 is X and dX.dim() == 2):
         dX = dX.view(*X.shape)
+    return dX, dB, dA, dbias
+
+
+def _backward_bf16_grads(dY, X, W, M, B, A, scale, mask_format, need_dx, need_dbias, ste):
+    """``backward`` with dB and dA rounded to bf16, the dtype of the adapters:
+    their fp32 sums and the workspace are one allocation, the rounding one
+    launch."""
+    X2, dY2 = _rows(X), _rows(dY)
+    dev = _dev(dY2, X2, W, M, B, A)
+    p = _problem(X2, W, B, mask_format, scale, flags=_lib.FLAG_BWD_STE if ste else 0)
+    ws = _lib.workspace_bytes(p)
+    if ws == 2**64 - 1:
+        raise ValueError("invalid problem")
+    nB, nA = p.R * p.r, p.r * p.C
+    offB = -(-ws // 256) * 256  # R and C are multiples of 8: every part stays 16-byte aligned
+    offA = offB + 4 * nB
+    scratch = torch.empty(offA + 4 * nA, dtype=torch.uint8, device=dev)
+    at = scratch.data_ptr()
+    dX = torch.empty(X.shape, dtype=W.dtype, device=dev) if need_dx else None
+    dbias = torch.empty(p.R, dtype=torch.float32, device=dev) if need_dbias else None
+    _call(dev, "lors_backward", _lib.backward, p, _ptr(dY2), _ptr(X2), _ptr(W), _ptr(M), _ptr(B), _ptr(A), _ptr(dX),
+          at + offB, at + offA, _ptr(dbias), at, ws)
+    dB = torch.empty(B.shape, dtype=torch.bfloat16, device=dev)
+    dA = torch.empty(A.shape, dtype=torch.bfloat16, device=dev)
+    _call(dev, "lors_round_bf16", _lib.round_bf16, at + offB, nB, _ptr(dB), at + offA, nA, _ptr(dA))
     return dX, dB, dA, dbias
 
 
@@ -209,10 +240,15 @@ class LoRSLinearFn(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dY):
         X, W, M, B, A = ctx.saved_tensors
-        dX, dB, dA, dbias = backward(dY.contiguous(), X, W, M, B, A, ctx.scale, ctx.mask_format,
-                                     need_dx=ctx.needs_input_grad[0], need_dbias=ctx.has_bias, ste=ctx.ste)
-        return (dX, None, None, dB.to(B.dtype), dA.to(A.dtype),
-                dbias.to(W.dtype) if dbias is not None else None, None, None, None)
+        need_dx = ctx.needs_input_grad[0]
+        if W.dtype == B.dtype == A.dtype == torch.bfloat16:
+            dX, dB, dA, dbias = _backward_bf16_grads(dY.contiguous(), X, W, M, B, A, ctx.scale, ctx.mask_format, need_dx,
+                                                     ctx.has_bias, ctx.ste)
+        else:
+            dX, dB, dA, dbias = backward(dY.contiguous(), X, W, M, B, A, ctx.scale, ctx.mask_format,
+                                         need_dx=need_dx, need_dbias=ctx.has_bias, ste=ctx.ste)
+            dB, dA = dB.to(B.dtype), dA.to(A.dtype)
+        return (dX, None, None, dB, dA, dbias.to(W.dtype) if dbias is not None else None, None, None, None)
 
 
 def lors_linear(X, W, M, B, A, scale, mask_format=BITMAP, bias=None, ste=False):

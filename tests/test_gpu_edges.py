@@ -166,3 +166,19 @@ def test_mask_words(dtype, R, C, fmt):
         val.view(R * C // 4, 4)[g] = 0
         with pytest.raises(ValueError, match=f"row {g // (C // 4)}, group {g % (C // 4)}"):
             ops.mask_pack(val.cuda(), fmt) if dtype == torch.uint8 else ops.mask_from_weight(val.cuda(), fmt)
+
+
+@pytest.mark.parametrize("na,nb", [(0, 5), (1, 0), (3, 4), (4096, 257), (1 << 20, 1 << 21)])
+def test_round_bf16(na, nb):
+    from paper_2501_08582_amd import _lib
+    g = torch.Generator(device="cuda").manual_seed(na + nb)
+    a, b = (torch.randn(n, generator=g, device="cuda") for n in (na, nb))
+    if na > 2:
+        a[:3] = torch.tensor([float("inf"), 2.0 ** -140, 1.00390625], device="cuda")  # the last one a tie
+    (ba, oa), (bb, ob) = (_guarded((n,), torch.bfloat16) for n in (na, nb))
+    _lib.check(_lib.round_bf16(a.data_ptr() if na else None, na, oa.data_ptr() if na else None,
+                               b.data_ptr() if nb else None, nb, ob.data_ptr() if nb else None,
+                               torch.cuda.current_stream().cuda_stream), "lors_round_bf16")
+    for buf, out, want in ((ba, oa, a), (bb, ob, b)):
+        assert torch.equal(out, want.to(torch.bfloat16))
+        assert torch.all(buf[:GUARD] == 0xA5) and torch.all(buf[GUARD + 2 * out.numel():] == 0xA5)
