@@ -69,12 +69,17 @@ __device__ __forceinline__ uint32_t ceil_div_u32(uint32_t a, uint32_t b) {
     return (a + b - 1) / b;
 }
 
-// Map a workgroup id to an output tile (tm, tn).
 // MI355X dispatches consecutive workgroup ids round-robin over its 8 XCDs,
-// each with a private L2.  When the grid divides evenly, ids are first
-// regrouped so that every XCD receives one contiguous range of logical tiles;
-// the logical order then walks `group_m` tile rows at a time, so the tiles an
-// XCD holds at once share few operand panels.
+// each with a private L2.  The ids 0 .. n-1 regrouped so that every XCD
+// receives one contiguous range of them (XCD x: the ids x, x + 8, ..).
+__device__ __forceinline__ int xcd_order(int bid, int n) {
+    const int x = bid & 7;
+    return x * (n >> 3) + min(x, n & 7) + (bid >> 3);
+}
+
+// Output tile (tm, tn) of logical tile t: the logical order walks `group_m`
+// tile rows at a time, so the tiles an XCD holds at once share few operand
+// panels.
 __device__ __forceinline__ void group_coords(int t, int tiles_m, int tiles_n, int group_m, int& tm, int& tn) {
     const int per_group = group_m * tiles_n;
     const int g = t / per_group;
@@ -87,10 +92,7 @@ __device__ __forceinline__ void group_coords(int t, int tiles_m, int tiles_n, in
 
 __device__ __forceinline__ void tile_coords(int bid, int tiles_m, int tiles_n, int group_m,
                                             int& tm, int& tn) {
-    const int total = tiles_m * tiles_n;
-    int t = bid;
-    if ((total & 7) == 0) t = (bid & 7) * (total >> 3) + (bid >> 3);
-    group_coords(t, tiles_m, tiles_n, group_m, tm, tn);
+    group_coords(xcd_order(bid, tiles_m * tiles_n), tiles_m, tiles_n, group_m, tm, tn);
 }
 
 // Tile and K-steps of a workgroup when the grid's last, partial wave of tiles
@@ -105,8 +107,7 @@ __device__ __forceinline__ void work_coords(int bid, int tiles_m, int tiles_n, i
                                             int split, int nk_all, int& tm, int& tn, int& kbeg, int& nk) {
     int t;
     if (bid < n_full) {
-        t = bid;
-        if ((n_full & 7) == 0) t = (bid & 7) * (n_full >> 3) + (bid >> 3);
+        t = xcd_order(bid, n_full);
         kbeg = 0;
         nk = nk_all;
     } else {
@@ -122,21 +123,13 @@ __device__ __forceinline__ void work_coords(int bid, int tiles_m, int tiles_n, i
 // Tile and sub-tile of a workgroup of a thin-tile grid (see thin_plan in
 // kernels.hpp): logical tiles first .. first+tail-1, in group_coords' order,
 // each cut into q sub-tiles u = 0 .. q-1, one per id (the kernel maps u to a
-// feature half and a token part).  When tail is a multiple of 8, the q
-// sub-tiles of a tile get ids of one XCD (ids are dealt to the 8 XCDs
-// round-robin), so they share its weight slabs in that XCD's L2.
+// feature half and a token part).  An XCD takes a contiguous range of them:
+// its tiles share weight and token panels in its L2.
 __device__ __forceinline__ void thin_coords(int bid, int tiles_m, int tiles_n, int group_m, int first, int tail,
                                             int q, int& tm, int& tn, int& u) {
-    int i;
-    if ((tail & 7) == 0) {
-        const int x = bid & 7, y = bid >> 3;
-        u = y % q;
-        i = 8 * (y / q) + x;
-    } else {
-        i = bid / q;
-        u = bid - i * q;
-    }
-    group_coords(first + i, tiles_m, tiles_n, group_m, tm, tn);
+    const int j = xcd_order(bid, tail * q);
+    u = j % q;
+    group_coords(first + j / q, tiles_m, tiles_n, group_m, tm, tn);
 }
 
 // Index of word iw (rows 32 iw .. 32 iw + 31 of R) of column col in the

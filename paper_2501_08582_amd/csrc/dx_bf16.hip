@@ -300,11 +300,13 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
     bf16x8 bfr[RK];           // B[32kb + pi(rho)][16c + 8h .. +7]
     bf16x8 afr[NF][RK];       // A[16c + 8h .. +7][n] (scaled by s when the merge is folded)
 
-    // MFMA slot i of a sub-step: token block i/2, feature block i%2 (the
-    // slots of token and feature blocks a thin tile lacks are empty)
+    // MFMA slot i of a sub-step: token block i/2, feature block i%2; the fewer
+    // MFMAs of a thin tile are spread over the 16 slots, so that the merge
+    // pieces of the later slots have some to hide behind
     auto mm = [&](int i, const bf16x8 (&df)[MBW], const u32x4 (&wf)[NF]) {
-        const int mb = i >> 1, nb = i & 1;
-        if (mb < MBW && nb < NF) acc[mb][nb] = mfma_32x32x16(df[mb], as_bf16x8(wf[nb]), acc[mb][nb]);
+        constexpr int kStep = 16 / (MBW * NF);
+        const int mb = i / (kStep * NF), nb = NF == 2 ? i & 1 : 0;
+        if (i % kStep == 0) acc[mb][nb] = mfma_32x32x16(df[mb], as_bf16x8(wf[nb]), acc[mb][nb]);
     };
     // ranks 16c + 8h .. +7 of B row 32kb + pik; the slab holds zeros for
     // ranks at or past r, so the read needs no per-lane test (a lane-dependent

@@ -298,11 +298,13 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
     u32x4 rwa[NF], rwb[NF];   // folded merge: W of the two sub-steps of a k half
     bf16x8 afr[RK];
 
-    // MFMA slot i of a sub-step: token block i/2, feature block i%2 (the
-    // slots of token and feature blocks a thin tile lacks are empty)
+    // MFMA slot i of a sub-step: token block i/2, feature block i%2; the fewer
+    // MFMAs of a thin tile are spread over the 16 slots, so that the merge
+    // pieces of the later slots have some to hide behind
     auto mm = [&](int i, const bf16x8 (&xf)[MBW], const u32x4 (&wf)[NF]) {
-        const int mb = i >> 1, nb = i & 1;
-        if (mb < MBW && nb < NF) acc[mb][nb] = mfma_32x32x16(xf[mb], as_bf16x8(wf[nb]), acc[mb][nb]);
+        constexpr int kStep = 16 / (MBW * NF);
+        const int mb = i / (kStep * NF), nb = NF == 2 ? i & 1 : 0;
+        if (i % kStep == 0) acc[mb][nb] = mfma_32x32x16(xf[mb], as_bf16x8(wf[nb]), acc[mb][nb]);
     };
     auto read_afr = [&](const uint8_t* sb, int kb) {
 #pragma unroll
