@@ -110,11 +110,13 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
     float* __restrict__ z1, int64_t nz1, int n_full, int split, float* __restrict__ part) {
     using Lay = Layout<RK, TM, NF>;
     constexpr int MBW = TM / 32;  // 32-token blocks per wave
+    constexpr int SPAN = thin_span(TM);  // tokens of a logical tile
     static_assert(NF == 1 || RK <= 4, "ranks above 64: half-feature tiles");
     static_assert(Lay::TOTAL <= 160 * 1024, "LDS budget");
     static_assert(4 * TM * 64 * NF <= Lay::S * Lay::STAGE, "output staging fits the stage buffers");
     // the prologue parks the merge's A block in the last PARK stages
-    constexpr int PARK = (16 * RK * kRowBytes + Lay::STAGE - 1) / Lay::STAGE;
+    constexpr int PROW = 2 * Lay::FT;
+    constexpr int PARK = (16 * RK * PROW + Lay::STAGE - 1) / Lay::STAGE;
     static_assert(PARK < Lay::S, "A block fits beside stage 0");
     __shared__ __attribute__((aligned(1024))) uint8_t smem[Lay::TOTAL];
 
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
 
     // tile and K-steps: ids past n_full are pieces of split tiles (their
     // partial sums go to `part`, see the epilogue).  Thin tiles: the grid
-    // covers logical tiles n_full .. n_full+split-1, each cut into BM/TM
+    // covers logical tiles n_full .. n_full+split-1, each cut into SPAN/TM
     // token parts of each of its 2/NF feature parts (see thin_coords), with
     // every K-step.
     int tm, tn;
@@ -150,11 +152,11 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
         n0 = tn * BN;
     } else {
         int u;
-        thin_coords(blockIdx.x, tiles_m, tiles_n, GROUP_M, n_full, split, (BM / TM) * (2 / NF), tm, tn, u);
+        thin_coords(blockIdx.x, tiles_m, tiles_n, GROUP_M, n_full, split, (SPAN / TM) * (2 / NF), tm, tn, u);
         kbeg = 0;
         nk = (R + BK - 1) / BK;
-        m0 = (int64_t)tm * BM + (int64_t)(u % (BM / TM)) * TM;
-        n0 = tn * BN + (u / (BM / TM)) * Lay::FT;
+        m0 = (int64_t)tm * SPAN + (int64_t)(u % (SPAN / TM)) * TM;
+        n0 = tn * BN + (u / (SPAN / TM)) * Lay::FT;
         if (m0 >= L || n0 >= C) return;  // a part of an edge tile that holds no output
     }
     // last row of the dY slab, last column chunk and last column that exist
@@ -306,7 +308,7 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
     auto mm = [&](int i, const bf16x8 (&df)[MBW], const u32x4 (&wf)[NF]) {
         constexpr int kStep = 16 / (MBW * NF);
         const int mb = i / (kStep * NF), nb = NF == 2 ? i & 1 : 0;
-        if (i % kStep == 0) acc[mb][nb] = mfma_32x32x16(df[mb], as_bf16x8(wf[nb]), acc[mb][nb]);
+        if (i % kStep == 0 && mb < MBW) acc[mb][nb] = mfma_32x32x16(df[mb], as_bf16x8(wf[nb]), acc[mb][nb]);
     };
     // ranks 16c + 8h .. +7 of B row 32kb + pik; the slab holds zeros for
     // ranks at or past r, so the read needs no per-lane test (a lane-dependent
@@ -439,13 +441,13 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
     // landed, the A block is read into registers and those stages are copied
     // over it (the K-steps' barriers wait for them), so the two round trips to
     // memory overlap.
-    // A[:, n0 .. n0+255] (16*RK rows)
+    // A[:, n0 .. n0+FT-1]: 16*RK rows of PROW bytes, chunks permuted as in tile_off
     constexpr int kPark = (Lay::S - PARK) * Lay::STAGE;
 #pragma unroll
-    for (int q = 0; q < 2 * RK; ++q) {
+    for (int q = 0; q < 16 * RK * PROW / 4096; ++q) {
         const int blk = 4 * q + wave;
-        const int row = 2 * blk + h;
-        const int lc = swz_chunk(row, lane & 31);
+        const int row = 1024 / PROW * blk + lane / (PROW / 16);
+        const int lc = swz_chunk(row, lane % (PROW / 16));
         const int gn = n0 + 8 * lc;
         copy16_to_lds((row < ra && gn < C) ? (const void*)(Am + (int64_t)row * C + gn) : (const void*)zsrc,
                       lds0 + kPark + 1024 * blk);
@@ -455,13 +457,19 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
 #pragma unroll
         for (int j = 0; j < Lay::COPIES; ++j) copy_j(j, (i < nk ? i : nk - 1) * BK, lds0 + i * Lay::STAGE);
     stage_barrier<(Lay::S - PARK - 1) * Lay::COPIES>();
-    // the merge's B operand A[16c + 8h + e][n] into registers via transpose loads
+    // the merge's B operand A[16c + 8h + e][n] into registers via transpose
+    // loads (lane and operand element as in tr_frag_off)
+    auto park_off = [&](int row0, int col0, int t) {
+        const int g = lane >> 4, j = lane & 15;
+        const int row = row0 + 8 * (g >> 1) + 4 * t + (j >> 2), col = col0 + 16 * (g & 1) + 4 * (j & 3);
+        return row * PROW + (swz_chunk(row, col >> 3) << 4) + ((col & 7) << 1);
+    };
 #pragma unroll
     for (int nb = 0; nb < NF; ++nb)
 #pragma unroll
         for (int c = 0; c < RK; ++c)
-            afr[nb][c] = frag_from_tr(lds_tr_read(smem + kPark + tr_frag_off(lane, 16 * c, 32 * NF * wave + 32 * nb, 0)),
-                                      lds_tr_read(smem + kPark + tr_frag_off(lane, 16 * c, 32 * NF * wave + 32 * nb, 1)));
+            afr[nb][c] = frag_from_tr(lds_tr_read(smem + kPark + park_off(16 * c, 32 * NF * wave + 32 * nb, 0)),
+                                      lds_tr_read(smem + kPark + park_off(16 * c, 32 * NF * wave + 32 * nb, 1)));
     if constexpr (FOLD) {  // s.A, exact for a power-of-two s
 #pragma unroll
         for (int nb = 0; nb < NF; ++nb)
@@ -627,12 +635,12 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st, int ra) {
     TailSplit sp{tiles, 1, tiles};
     if (a.split_ws != nullptr && !dx_whole_tiles(a.L, a.R, a.C))
         sp = tail_split(tiles, (a.R + BK - 1) / BK, a.split_budget);
-    const ThinPlan tp = sp.split == 1 ? thin_plan(tiles) : ThinPlan{tiles, 0, 1};
+    const ThinPlan tp = sp.split == 1 ? thin_plan(a.L, a.C) : ThinPlan{tiles, 0, 0};
     float* part = sp.split > 1 ? (float*)a.split_ws : nullptr;
     // with thin tiles the whole-tile grid is exactly the first n_full tiles
     // (work_coords regroups ids over the tiles it is told the grid holds)
-    const int grid = tp.q > 1 ? tp.n_full : sp.grid;
-    const int n_full = tp.q > 1 ? tp.n_full : sp.n_full;
+    const int grid = tp.tm > 0 ? tp.n_full : sp.grid;
+    const int n_full = tp.tm > 0 ? tp.n_full : sp.n_full;
     // clear: dB (R x rank) and dA (rank x C) of the caller's problem, by the
     // first launch of this call
     const bool clear_here = a.clear_grads && grid > 0;
@@ -651,8 +659,8 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st, int ra) {
                                                    z0, nz0, z1, nz1);
     }
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && tp.q > 1)
-        e = launch_dx_thin_bf16(a, st, ra, tp.n_full, tp.tail, tp.q, a.clear_grads && !clear_here);
+    if (e == hipSuccess && tp.tm > 0)
+        e = launch_dx_thin_bf16(a, st, ra, tp.n_full, tp.tail, tp.tm, a.clear_grads && !clear_here);
     if (e == hipSuccess && sp.split > 1)
         e = launch_split_reduce_bf16(part, sp.n_full, sp.split, tiles_m, tiles_n, GROUP_M, a.L, (int)a.C, nullptr,
                                      a.dX, st);
@@ -661,36 +669,37 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st, int ra) {
 
 #else  // LORS_THIN_TILES
 
-// thin tiles of one feature half (NF = 1) and TM tokens: 2 BM / TM per tile
+// thin tiles of one feature half (NF = 1) and TM tokens: 2 SPAN / TM per tile
 template <int RK, bool KRAG, bool FOLD, int TM>
 hipError_t launch_thin_tm(const LayerArgs& a, hipStream_t st, int ra, int first, int tail, bool clear) {
-    const int tiles_m = (int)((a.L + BM - 1) / BM);
+    const int tiles_m = (int)((a.L + thin_span(TM) - 1) / thin_span(TM));
     const int tiles_n = (int)((a.C + BN - 1) / BN);
     float* z0 = clear ? a.dB : nullptr;
     float* z1 = clear ? a.dA : nullptr;
     const int64_t nz0 = clear ? a.R * a.r_grad : 0, nz1 = clear ? a.r_grad * a.C : 0;
-    launch_tm<RK, KRAG, FOLD, TM, 1>(a, st, ra, tail * (2 * BM / TM), tiles_m, tiles_n, first, tail, nullptr,
+    launch_tm<RK, KRAG, FOLD, TM, 1>(a, st, ra, tail * (2 * thin_span(TM) / TM), tiles_m, tiles_n, first, tail, nullptr,
                                           z0, nz0, z1, nz1);
     return hipGetLastError();
 }
 
 template <int RK, bool KRAG, bool FOLD>
-hipError_t launch_thin_q(const LayerArgs& a, hipStream_t st, int ra, int first, int tail, int q,
+hipError_t launch_thin_q(const LayerArgs& a, hipStream_t st, int ra, int first, int tail, int tm,
                          bool clear) {
-    switch (q) {  // q thin tiles per tile: two feature halves, each cut into q/2 token parts
-        case 2: return launch_thin_tm<RK, KRAG, FOLD, BM>(a, st, ra, first, tail, clear);
-        case 4: return launch_thin_tm<RK, KRAG, FOLD, BM / 2>(a, st, ra, first, tail, clear);
-        case 8: return launch_thin_tm<RK, KRAG, FOLD, BM / 4>(a, st, ra, first, tail, clear);
+    switch (tm) {
+        case 64: return launch_thin_tm<RK, KRAG, FOLD, 64>(a, st, ra, first, tail, clear);
+        case 128: return launch_thin_tm<RK, KRAG, FOLD, 128>(a, st, ra, first, tail, clear);
+        case 192: return launch_thin_tm<RK, KRAG, FOLD, 192>(a, st, ra, first, tail, clear);
+        case 256: return launch_thin_tm<RK, KRAG, FOLD, 256>(a, st, ra, first, tail, clear);
         default: return hipErrorInvalidValue;
     }
 }
 
 template <int RK>
-hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int ra, int first, int tail, int q,
+hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int ra, int first, int tail, int tm,
                           bool clear) {
-    if (!dx_fixed_copies(a.R, a.C)) return launch_thin_q<RK, true, false>(a, st, ra, first, tail, q, clear);
-    return power_of_two(a.scale) ? launch_thin_q<RK, false, true>(a, st, ra, first, tail, q, clear)
-                                 : launch_thin_q<RK, false, false>(a, st, ra, first, tail, q, clear);
+    if (!dx_fixed_copies(a.R, a.C)) return launch_thin_q<RK, true, false>(a, st, ra, first, tail, tm, clear);
+    return power_of_two(a.scale) ? launch_thin_q<RK, false, true>(a, st, ra, first, tail, tm, clear)
+                                 : launch_thin_q<RK, false, false>(a, st, ra, first, tail, tm, clear);
 }
 
 #endif  // LORS_THIN_TILES
@@ -699,19 +708,19 @@ hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int ra, int first,
 
 #ifdef LORS_THIN_TILES
 
-hipError_t launch_dx_thin_bf16(const LayerArgs& a, hipStream_t st, int ra, int first, int tail, int q, bool clear) {
+hipError_t launch_dx_thin_bf16(const LayerArgs& a, hipStream_t st, int ra, int first, int tail, int tm, bool clear) {
     if (tail <= 0) return hipSuccess;
     // a.r: a multiple of 8 (see launch_dx_bf16)
     if (a.r < 8 || a.r % 8 != 0) return hipErrorInvalidValue;
     switch ((a.r + 15) / 16) {
-        case 1: return launch_thin_rk<1>(a, st, ra, first, tail, q, clear);
-        case 2: return launch_thin_rk<2>(a, st, ra, first, tail, q, clear);
-        case 3: return launch_thin_rk<3>(a, st, ra, first, tail, q, clear);
-        case 4: return launch_thin_rk<4>(a, st, ra, first, tail, q, clear);
-        case 5: return launch_thin_rk<5>(a, st, ra, first, tail, q, clear);
-        case 6: return launch_thin_rk<6>(a, st, ra, first, tail, q, clear);
-        case 7: return launch_thin_rk<7>(a, st, ra, first, tail, q, clear);
-        case 8: return launch_thin_rk<8>(a, st, ra, first, tail, q, clear);
+        case 1: return launch_thin_rk<1>(a, st, ra, first, tail, tm, clear);
+        case 2: return launch_thin_rk<2>(a, st, ra, first, tail, tm, clear);
+        case 3: return launch_thin_rk<3>(a, st, ra, first, tail, tm, clear);
+        case 4: return launch_thin_rk<4>(a, st, ra, first, tail, tm, clear);
+        case 5: return launch_thin_rk<5>(a, st, ra, first, tail, tm, clear);
+        case 6: return launch_thin_rk<6>(a, st, ra, first, tail, tm, clear);
+        case 7: return launch_thin_rk<7>(a, st, ra, first, tail, tm, clear);
+        case 8: return launch_thin_rk<8>(a, st, ra, first, tail, tm, clear);
         default: return hipErrorInvalidValue;
     }
 }
@@ -742,12 +751,11 @@ hipError_t launch_dx_bf16(const LayerArgs& a, hipStream_t st) {
         default: break;
     }
     // ranks above 64: half-feature thin tiles only (see the forward)
-    int first[2], tail[2], q[2];
-    const int64_t tiles = ((a.L + BM - 1) / BM) * ((a.C + BN - 1) / BN);
-    const int n = thin_only_plan(tiles, first, tail, q);
+    ThinPlan run[2];
+    const int n = thin_only_plan(a.L, a.C, run);
     hipError_t e = hipSuccess;
     for (int i = 0; i < n && e == hipSuccess; ++i)
-        e = launch_dx_thin_bf16(ap, st, ra, first[i], tail[i], q[i], a.clear_grads && i == 0);
+        e = launch_dx_thin_bf16(ap, st, ra, run[i].n_full, run[i].tail, run[i].tm, a.clear_grads && i == 0);
     return e;
 }
 

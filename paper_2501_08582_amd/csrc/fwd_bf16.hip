@@ -111,6 +111,7 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
     int tiles_n, int n_full, int split, float* __restrict__ part, int two_four) {
     using Lay = Layout<RK, TM, NF>;
     constexpr int MBW = TM / 32;  // 32-token blocks per wave
+    constexpr int SPAN = thin_span(TM);  // tokens of a logical tile
     static_assert(NF == 1 || RK <= 4, "ranks above 64: half-feature tiles");
     static_assert(Lay::TOTAL <= 160 * 1024, "LDS budget");
     static_assert(4 * TM * 64 * NF <= Lay::S * Lay::STAGE, "output staging fits the stage buffers");
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
 
     // tile and K-steps: ids past n_full are pieces of split tiles (their
     // partial sums go to `part`, see the epilogue).  Thin tiles: the grid
-    // covers logical tiles n_full .. n_full+split-1, each cut into BM/TM
+    // covers logical tiles n_full .. n_full+split-1, each cut into SPAN/TM
     // token parts of each of its 2/NF feature parts (see thin_coords), with
     // every K-step.
     int tm, tn;
@@ -137,11 +138,11 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
         n0 = tn * BN;
     } else {
         int u;
-        thin_coords(blockIdx.x, tiles_m, tiles_n, GROUP_M, n_full, split, (BM / TM) * (2 / NF), tm, tn, u);
+        thin_coords(blockIdx.x, tiles_m, tiles_n, GROUP_M, n_full, split, (SPAN / TM) * (2 / NF), tm, tn, u);
         kbeg = 0;
         nk = (C + BK - 1) / BK;
-        m0 = (int64_t)tm * BM + (int64_t)(u % (BM / TM)) * TM;
-        n0 = tn * BN + (u / (BM / TM)) * Lay::FT;
+        m0 = (int64_t)tm * SPAN + (int64_t)(u % (SPAN / TM)) * TM;
+        n0 = tn * BN + (u / (SPAN / TM)) * Lay::FT;
         if (m0 >= L || n0 >= R) return;  // a part of an edge tile that holds no output
     }
     // last rows of the X and W slabs that exist
@@ -304,7 +305,7 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
     auto mm = [&](int i, const bf16x8 (&xf)[MBW], const u32x4 (&wf)[NF]) {
         constexpr int kStep = 16 / (MBW * NF);
         const int mb = i / (kStep * NF), nb = NF == 2 ? i & 1 : 0;
-        if (i % kStep == 0) acc[mb][nb] = mfma_32x32x16(xf[mb], as_bf16x8(wf[nb]), acc[mb][nb]);
+        if (i % kStep == 0 && mb < MBW) acc[mb][nb] = mfma_32x32x16(xf[mb], as_bf16x8(wf[nb]), acc[mb][nb]);
     };
     auto read_afr = [&](const uint8_t* sb, int kb) {
 #pragma unroll
@@ -594,12 +595,12 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st) {
     TailSplit sp{tiles, 1, tiles};
     if (a.split_ws != nullptr && !fwd_whole_tiles(a.L, a.R, a.C))
         sp = tail_split(tiles, (a.C + BK - 1) / BK, a.split_budget);
-    const ThinPlan tp = sp.split == 1 ? thin_plan(tiles) : ThinPlan{tiles, 0, 1};
+    const ThinPlan tp = sp.split == 1 ? thin_plan(a.L, a.R) : ThinPlan{tiles, 0, 0};
     float* part = sp.split > 1 ? (float*)a.split_ws : nullptr;
     // with thin tiles the whole-tile grid is exactly the first n_full tiles
     // (work_coords regroups ids over the tiles it is told the grid holds)
-    const int grid = tp.q > 1 ? tp.n_full : sp.grid;
-    const int n_full = tp.q > 1 ? tp.n_full : sp.n_full;
+    const int grid = tp.tm > 0 ? tp.n_full : sp.grid;
+    const int n_full = tp.tm > 0 ? tp.n_full : sp.n_full;
     if (grid > 0) {
         if (krag)
             launch_whole<RK, true, false>(a, st, grid, tiles_m, tiles_n, n_full, sp.split,
@@ -612,7 +613,7 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st) {
                                                             part);
     }
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && tp.q > 1) e = launch_fwd_thin_bf16(a, st, tp.n_full, tp.tail, tp.q);
+    if (e == hipSuccess && tp.tm > 0) e = launch_fwd_thin_bf16(a, st, tp.n_full, tp.tail, tp.tm);
     if (e == hipSuccess && sp.split > 1)
         e = launch_split_reduce_bf16(part, sp.n_full, sp.split, tiles_m, tiles_n, GROUP_M, a.L, (int)a.R, a.bias,
                                      a.Y, st);
@@ -621,12 +622,12 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st) {
 
 #else  // LORS_THIN_TILES
 
-// thin tiles of one feature half (NF = 1) and TM tokens: 2 BM / TM per tile
+// thin tiles of one feature half (NF = 1) and TM tokens: 2 SPAN / TM per tile
 template <int RK, bool KRAG, bool FOLD, int TM>
 hipError_t launch_thin_tm(const LayerArgs& a, hipStream_t st, int first, int tail) {
-    const int tiles_m = (int)((a.L + BM - 1) / BM);
+    const int tiles_m = (int)((a.L + thin_span(TM) - 1) / thin_span(TM));
     const int tiles_n = (int)((a.R + BN - 1) / BN);
-    hipLaunchKernelGGL((fwd_kernel<RK, KRAG, FOLD, TM, 1>), dim3(tail * (2 * BM / TM)), dim3(NT), 0, st,
+    hipLaunchKernelGGL((fwd_kernel<RK, KRAG, FOLD, TM, 1>), dim3(tail * (2 * thin_span(TM) / TM)), dim3(NT), 0, st,
                        (const uint16_t*)a.X, (const uint16_t*)a.W, a.M, (const uint16_t*)a.B,
                        (const uint16_t*)a.A, (const uint16_t*)a.bias, (uint16_t*)a.Y, a.L, (int)a.R, (int)a.C,
                        (int)a.r, a.scale, tiles_m, tiles_n, first, tail, (float*)nullptr,
@@ -635,22 +636,23 @@ hipError_t launch_thin_tm(const LayerArgs& a, hipStream_t st, int first, int tai
 }
 
 template <int RK, bool KRAG, bool FOLD>
-hipError_t launch_thin_q(const LayerArgs& a, hipStream_t st, int first, int tail, int q) {
-    switch (q) {  // q thin tiles per tile: two feature halves, each cut into q/2 token parts
-        case 2: return launch_thin_tm<RK, KRAG, FOLD, BM>(a, st, first, tail);
-        case 4: return launch_thin_tm<RK, KRAG, FOLD, BM / 2>(a, st, first, tail);
-        case 8: return launch_thin_tm<RK, KRAG, FOLD, BM / 4>(a, st, first, tail);
+hipError_t launch_thin_q(const LayerArgs& a, hipStream_t st, int first, int tail, int tm) {
+    switch (tm) {
+        case 64: return launch_thin_tm<RK, KRAG, FOLD, 64>(a, st, first, tail);
+        case 128: return launch_thin_tm<RK, KRAG, FOLD, 128>(a, st, first, tail);
+        case 192: return launch_thin_tm<RK, KRAG, FOLD, 192>(a, st, first, tail);
+        case 256: return launch_thin_tm<RK, KRAG, FOLD, 256>(a, st, first, tail);
         default: return hipErrorInvalidValue;
     }
 }
 
 template <int RK>
-hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int first, int tail, int q) {
+hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int first, int tail, int tm) {
     const bool krag = !fwd_fixed_copies(a.C);
     const bool fold = !krag && power_of_two(a.scale);
-    return krag   ? launch_thin_q<RK, true, false>(a, st, first, tail, q)
-           : fold ? launch_thin_q<RK, false, true>(a, st, first, tail, q)
-                  : launch_thin_q<RK, false, false>(a, st, first, tail, q);
+    return krag   ? launch_thin_q<RK, true, false>(a, st, first, tail, tm)
+           : fold ? launch_thin_q<RK, false, true>(a, st, first, tail, tm)
+                  : launch_thin_q<RK, false, false>(a, st, first, tail, tm);
 }
 
 #endif  // LORS_THIN_TILES
@@ -687,27 +689,27 @@ hipError_t launch_fwd_bf16(const LayerArgs& a, hipStream_t st) {
     // One pass: 104 us at 4096 x 4096, 2048 tokens, rank 128, against 211 us
     // for two passes of whole tiles over the ranks below and above 64, the
     // second adding onto Y (dX: 107 against 211).
-    int first[2], tail[2], q[2];
-    const int64_t tiles = ((a.L + BM - 1) / BM) * ((a.R + BN - 1) / BN);
-    const int n = thin_only_plan(tiles, first, tail, q);
+    ThinPlan run[2];
+    const int n = thin_only_plan(a.L, a.R, run);
     hipError_t e = hipSuccess;
-    for (int i = 0; i < n && e == hipSuccess; ++i) e = launch_fwd_thin_bf16(a, st, first[i], tail[i], q[i]);
+    for (int i = 0; i < n && e == hipSuccess; ++i)
+        e = launch_fwd_thin_bf16(a, st, run[i].n_full, run[i].tail, run[i].tm);
     return e;
 }
 
 #else
 
-hipError_t launch_fwd_thin_bf16(const LayerArgs& a, hipStream_t st, int first, int tail, int q) {
+hipError_t launch_fwd_thin_bf16(const LayerArgs& a, hipStream_t st, int first, int tail, int tm) {
     if (tail <= 0) return hipSuccess;
     switch ((a.r + 15) / 16) {
-        case 1: return launch_thin_rk<1>(a, st, first, tail, q);
-        case 2: return launch_thin_rk<2>(a, st, first, tail, q);
-        case 3: return launch_thin_rk<3>(a, st, first, tail, q);
-        case 4: return launch_thin_rk<4>(a, st, first, tail, q);
-        case 5: return launch_thin_rk<5>(a, st, first, tail, q);
-        case 6: return launch_thin_rk<6>(a, st, first, tail, q);
-        case 7: return launch_thin_rk<7>(a, st, first, tail, q);
-        case 8: return launch_thin_rk<8>(a, st, first, tail, q);
+        case 1: return launch_thin_rk<1>(a, st, first, tail, tm);
+        case 2: return launch_thin_rk<2>(a, st, first, tail, tm);
+        case 3: return launch_thin_rk<3>(a, st, first, tail, tm);
+        case 4: return launch_thin_rk<4>(a, st, first, tail, tm);
+        case 5: return launch_thin_rk<5>(a, st, first, tail, tm);
+        case 6: return launch_thin_rk<6>(a, st, first, tail, tm);
+        case 7: return launch_thin_rk<7>(a, st, first, tail, tm);
+        case 8: return launch_thin_rk<8>(a, st, first, tail, tm);
         default: return hipErrorInvalidValue;
     }
 }

@@ -53,25 +53,33 @@ TailSplit tail_split(int64_t tiles, int64_t nk, int64_t max_part_bytes);
 inline int64_t split_part_bytes(const TailSplit& t) {
     return t.split > 1 ? (int64_t)(t.grid - t.n_full) * kPieceBytes : 0;
 }
-// A short last wave of 256 x 256 tiles cut into thin tiles instead: each of
-// its `tail` tiles becomes q thin tiles (q = 2, 4 or 8, as many as fill the
-// CUs; q = 1: not cut) -- its two halves of 128 output features, each cut
-// over the tokens into q/2 parts of 512/q tokens.  A thin tile runs the whole
-// K-loop with the same per-element arithmetic as a whole tile, so its
-// results are the same bits, and it needs no workspace.  Its waves merge 32
-// rows of W' each instead of 64, so the merge shrinks with the tile, though
-// less than the matrix work does when the tokens are cut too.  Applies to a
-// wave that fills at most half of the CUs, like tail_split.
-// n_full: the tiles that run whole (the first n_full in the kernels' order).
+// A short last wave of 256 x 256 tiles cut into thin tiles instead: each of its
+// `tail` tiles becomes two halves of 128 output features, each cut over the
+// tokens into 256/tm parts (tm = 256, 128 or 64; tm = 0: no such wave) -- as
+// many thin tiles as fit on the CUs.  A thin tile runs the whole K-loop with
+// the same per-element arithmetic as a whole tile, so its results are the same
+// bits, and it needs no workspace.  Its waves merge 32 rows of W' each instead
+// of 64, so the merge shrinks with the tile, though less than the matrix work
+// does when the tokens are cut too.  Applies to a wave that fills at most half
+// of the CUs, like tail_split.  A grid that is one such wave (no whole wave
+// before it) takes its token count from a cost of a K-step, 192 among them:
+// 0.45 + 0.0042 tm us were measured (5120 x 5120 and 4096 x 14336, rank 64:
+// 0.72 us at 64 tokens, 1.02 at 128, 1.5 at 256), times the rounds that
+// ceil(L/tm) ceil(N/128) thin tiles take on the CUs.
+// n_full: the tiles that run whole (the first n_full in the kernels' order);
+// for tm = 192 n_full = 0 and the logical tiles are 192 x 256.
 struct ThinPlan {
-    int n_full, tail, q;
+    int n_full, tail, tm;
 };
-ThinPlan thin_plan(int64_t tiles);
-// A grid of thin tiles only: the tiles' runs [first, first + tail) and the q
-// of each, one launch per run (at most two, the count is returned).  Whole
-// waves run as feature halves (q = 2); a short last wave, or a grid that is
-// one, takes the larger q of thin_plan's rule.
-int thin_only_plan(int64_t tiles, int first[2], int tail[2], int q[2]);
+// tokens of the logical tile that thin tiles of tm tokens are cut from
+constexpr int thin_span(int tm) { return tm == 192 ? 192 : 256; }
+// L x N: the output
+ThinPlan thin_plan(int64_t L, int64_t N);
+// A grid of thin tiles only: its runs of tiles (n_full: a run's first tile),
+// one launch per run, at most two; the count is returned.  Whole waves run as
+// feature halves of 256 tokens; a short last wave, or a grid that is one, as
+// thin_plan's.
+int thin_only_plan(int64_t L, int64_t N, ThinPlan run[2]);
 // Shapes of whole tiles, which never split over K: 256 x 256 tiles and 64-wide
 // K-steps cover the forward's L x R, K = C (dX's L x C, K = R) exactly.
 inline bool fwd_whole_tiles(int64_t L, int64_t R, int64_t C) {
@@ -99,11 +107,11 @@ hipError_t launch_fwd_bf16(const LayerArgs& a, hipStream_t s);
 hipError_t launch_fwd_few_bf16(const LayerArgs& a, hipStream_t s);  // few tokens
 hipError_t launch_fwd24_bf16(const LayerArgs& a, hipStream_t s);      // 2:4 mask, sparse MFMA, rank <= 64
 hipError_t launch_dx_bf16(const LayerArgs& a, hipStream_t s);
-// Thin tiles (see ThinPlan): logical tiles first .. first+tail-1, each cut
-// into q.  ra: rows of A that exist; clear: the launch also clears dB and dA
+// Thin tiles of tm tokens (see ThinPlan) of the logical tiles first ..
+// first+tail-1.  ra: rows of A that exist; clear: the launch also clears dB and dA
 // (it is the first of the dX launches).
-hipError_t launch_fwd_thin_bf16(const LayerArgs& a, hipStream_t s, int first, int tail, int q);
-hipError_t launch_dx_thin_bf16(const LayerArgs& a, hipStream_t s, int ra, int first, int tail, int q, bool clear);
+hipError_t launch_fwd_thin_bf16(const LayerArgs& a, hipStream_t s, int first, int tail, int tm);
+hipError_t launch_dx_thin_bf16(const LayerArgs& a, hipStream_t s, int ra, int first, int tail, int tm, bool clear);
 hipError_t launch_g_bf16(const LayerArgs& a, hipStream_t s);
 hipError_t launch_ste_bf16(const LayerArgs& a, hipStream_t s);  // dB, dA of the straight-through backward
 size_t ste_workspace_bytes(int64_t R, int64_t L, int64_t r);

@@ -403,30 +403,44 @@ TailSplit tail_split(int64_t tiles, int64_t nk, int64_t max_part_bytes) {
     return t;
 }
 
-ThinPlan thin_plan(int64_t tiles) {
-    const int cus = device_cus();
-    ThinPlan t{(int)tiles, 0, 1};
-    const int64_t tail = tiles % cus;
-    if (tail == 0 || 2 * tail > cus) return t;
-    int q = 2;
-    while (q < 8 && 2 * q * tail <= cus) q *= 2;
-    t.n_full = (int)(tiles - tail);
-    t.tail = (int)tail;
-    t.q = q;
-    return t;
+// the thin tiles of a grid that is one short wave
+static ThinPlan thin_grid(int64_t L, int64_t N, int cus) {
+    int best = 256;
+    double least = 0;
+    for (int tm = 256; tm >= 64; tm -= 64) {
+        const int64_t wgs = ((L + tm - 1) / tm) * ((N + 127) / 128);
+        const double cost = (double)((wgs + cus - 1) / cus) * (0.45 + 0.0042 * tm);
+        if (tm == 256 || cost < least) {
+            least = cost;
+            best = tm;
+        }
+    }
+    const int64_t span = thin_span(best);
+    return ThinPlan{0, (int)(((L + span - 1) / span) * ((N + 255) / 256)), best};
 }
 
-int thin_only_plan(int64_t tiles, int first[2], int tail[2], int q[2]) {
+static int64_t tiles256(int64_t L, int64_t N) { return ((L + 255) / 256) * ((N + 255) / 256); }
+
+ThinPlan thin_plan(int64_t L, int64_t N) {
     const int cus = device_cus();
-    const int64_t rest = (2 * tiles % cus + 1) / 2;  // tiles of the last wave of feature halves
-    const int whole = (int)(4 * rest <= cus ? tiles - rest : tiles);
-    int n = 0;
-    if (whole > 0) { first[n] = 0; tail[n] = whole; q[n++] = 2; }
-    if (whole < tiles) {
-        const int t = (int)(tiles - whole);
-        first[n] = whole; tail[n] = t; q[n++] = 8 * t <= cus ? 8 : 4;
+    const int64_t tiles = tiles256(L, N), tail = tiles % cus;
+    if (tail == 0 || 2 * tail > cus) return ThinPlan{(int)tiles, 0, 0};
+    if (tail == tiles) return thin_grid(L, N, cus);
+    return ThinPlan{(int)(tiles - tail), (int)tail, 8 * tail <= cus ? 64 : 4 * tail <= cus ? 128 : 256};
+}
+
+int thin_only_plan(int64_t L, int64_t N, ThinPlan run[2]) {
+    const int cus = device_cus();
+    const int64_t tiles = tiles256(L, N);
+    if (2 * tiles <= cus) {
+        run[0] = thin_grid(L, N, cus);
+        return 1;
     }
-    return n;
+    const int64_t rest = (2 * tiles % cus + 1) / 2;  // tiles of the last wave of feature halves
+    const bool cut = rest > 0 && 4 * rest <= cus;
+    run[0] = ThinPlan{0, (int)(cut ? tiles - rest : tiles), 256};
+    run[1] = ThinPlan{(int)(tiles - rest), (int)rest, 8 * rest <= cus ? 64 : 128};
+    return cut ? 2 : 1;
 }
 
 hipError_t launch_zero2_f32(float* a, int64_t na, float* b, int64_t nb, hipStream_t st) {

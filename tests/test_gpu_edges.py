@@ -41,6 +41,9 @@ def _guarded(shape, dtype):
     (4160, 4224, 513, 16, "magnitude", 2.0),  # three token tiles, the last of one token
     (256, 256, 300, 100, "magnitude", 2.0),   # ranks above 64: feature halves, no whole wave
     (264, 328, 193, 72, "2:4", 0.3),
+    (4096, 192, 1100, 24, "magnitude", 2.0),  # forward: a grid of 192-token thin tiles
+    (192, 4160, 1090, 24, "2:4", 1.5),        # dX: the same
+    (200, 4096, 1100, 128, "2:4", 2.0),       # dX: the same above rank 64, checked copies
     (320, 4160, 2300, 128, "magnitude", 1.0), # dX: a wave of feature halves, then thinner tiles
 ])
 def test_edges(R, C, L, r, mask, scale):
