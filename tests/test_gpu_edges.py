@@ -185,3 +185,20 @@ def test_round_bf16(na, nb):
     for buf, out, want in ((ba, oa, a), (bb, ob, b)):
         assert torch.equal(out, want.to(torch.bfloat16))
         assert torch.all(buf[:GUARD] == 0xA5) and torch.all(buf[GUARD + 2 * out.numel():] == 0xA5)
+
+
+# the transposed mask, through the weight gradient it masks: rows and columns
+# that end inside a word, a pair of words and a workgroup's 16 words
+@pytest.mark.parametrize("R,C,mask", [(8, 8, "magnitude"), (72, 520, "2:4"), (96, 48, "magnitude"), (136, 1032, "2:4"),
+                                      (64, 2048, "2:4"), (1000, 40, "magnitude")])
+def test_transposed_mask(R, C, mask):
+    name = "llama2_7b_up_proj_2_4" if mask == "2:4" else "llama2_7b_q_proj"
+    inp = synth.make(synth.workload(name).with_(R=R, C=C, r=8, seed=8000 + R), L=32)
+    X, W, B, A, dY = (to_dev(t, "bf16") for t in (inp.X, inp.W, inp.B, inp.A, inp.dY))
+    M = ops.mask_pack(torch.from_numpy(inp.M).cuda(), FMT[mask])
+    _, dB, dA, _ = ops.backward(dY, X, W, M, B, A, 2.0, FMT[mask], need_dx=False)
+    x, w, b, a, dy = (to_f64(t, "bf16") for t in (inp.X, inp.W, inp.B, inp.A, inp.dY))
+    _, rdB, rdA, _ = olors.backward(dy, x, w, inp.M, b, a, 2.0)
+    for k, got, want in (("dB", dB, rdB), ("dA", dA, rdA)):
+        err, at = worst_tile(dev_to_f64(got), want, (8, 8))
+        assert err <= TOL["bf16"], f"{k} block {at}: rel err {err:.3e}"
