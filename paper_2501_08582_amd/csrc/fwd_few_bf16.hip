@@ -3,8 +3,8 @@
 //   Y[L x R] = X[L x C] . W'^T,   W' = select(M, W + s.B.A, 0)
 //
 // With a handful of tokens the layer is one read of W, so the work is cut for
-// the memory system and not for the matrix cores: a workgroup owns FT = 16 or
-// 32 output features and MB blocks of FT tokens, and its waves share the
+// the memory system and not for the matrix cores: a workgroup owns NB blocks of
+// FT = 16 or 32 output features and MB blocks of FT tokens, and its waves share the
 // contraction (64-k block j belongs to wave j mod NW), so that a few thousand
 // features already put thousands of waves, each with several loads in flight,
 // on the chip.  Nothing is shared inside the K-loop and it has no barrier:
@@ -39,7 +39,7 @@ __device__ __forceinline__ void store8(const float (&sum)[8], int gm, int gn, in
     *(u32x4*)(Y + (int64_t)gm * R + gn) = o;
 }
 
-template <int FT, int RK, int MB>
+template <int FT, int RK, int MB, int NB>
 struct Cfg {
     static constexpr int G = 64 / FT;           // lane groups: lane l holds column l % FT, k 8(l/FT) .. +7
     static constexpr int WV = 8 / G;            // operand vectors of a block: vector c holds k 8Gc ..
@@ -49,48 +49,53 @@ struct Cfg {
     static constexpr int AW = RM * RC * kRow64; // one wave's A slab
     // Registers: a block in flight, and about what the rest of a wave needs.
     // FT = 16 (few workgroups) takes as many waves as hold two blocks each,
-    // and a third block where it fits; FT = 32 two blocks, so that two
+    // and a third block where it fits; FT = 32 two blocks, so that with NB = 1 two
     // workgroups share a CU where the registers allow (14336 x 4096, 32 tokens:
     // 44 us, against 49 with three blocks in flight and one workgroup).
     static constexpr bool XA = FT == 16 && MB <= 2;  // X is fetched ahead too (else inside its block: it is in L2)
-    static constexpr int BLOCK = 4 * WV + 2 + 8 * RK + (XA ? 4 * WV * MB : 0);
-    static constexpr int OTHER = 56 + 4 * RC + 2 * RK + NV * (MB + 1) + (XA ? 0 : 4 * WV * MB);
+    static constexpr int BLOCK = NB * (4 * WV + 2) + 8 * RK + (XA ? 4 * WV * MB : 0);
+    static constexpr int OTHER = 56 + 4 * RC * NB + 2 * RK + NV * (MB * NB + 1) + (XA ? 0 : 4 * WV * MB);
     static constexpr int NW = FT == 16 && 2 * BLOCK + OTHER <= 128 ? 16 : 2 * BLOCK + OTHER <= 256 ? 8 : 4;
     static constexpr int SLOTS = FT == 16 && 3 * BLOCK + OTHER <= 2048 / NW ? 3 : 2;
-    static constexpr int EU = FT == 32 && RK == 1 && MB == 1 ? 4 : NW / 4;  // waves per SIMD
-    static constexpr int RED = NW * MB * NV * 64 * 4;    // the waves' partial sums (after the loop)
+    static constexpr int EU = FT == 32 && RK == 1 && MB == 1 && NB == 1 ? 4 : NW / 4;  // waves per SIMD
+    static constexpr int RED = NW * NB * MB * NV * 64 * 4;    // the waves' partial sums (after the loop)
     static constexpr int LUT = NW * AW > RED ? NW * AW : RED;
     static constexpr int TOTAL = LUT + 128;
 };
 
 // KRAG: C is no multiple of 64; chunks past C are read from the row's first
 // chunk and dropped by zero W' and zero X.
-template <int FT, int RK, bool KRAG, int MB>
-__global__ __launch_bounds__((64 * Cfg<FT, RK, MB>::NW), (Cfg<FT, RK, MB>::EU)) void fwd_few_kernel(
+template <int FT, int RK, bool KRAG, int MB, int NB>
+__global__ __launch_bounds__((64 * Cfg<FT, RK, MB, NB>::NW), (Cfg<FT, RK, MB, NB>::EU)) void fwd_few_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, const uint32_t* __restrict__ Mp,
     const uint16_t* __restrict__ Bm, const uint16_t* __restrict__ Am, const uint16_t* __restrict__ bias,
     uint16_t* __restrict__ Y, int L, int R, int C, int r, float s, int two_four) {
-    using T = Cfg<FT, RK, MB>;
+    using T = Cfg<FT, RK, MB, NB>;
     constexpr int NW = T::NW, G = T::G, WV = T::WV, RC = T::RC, NV = T::NV, SLOTS = T::SLOTS;
     static_assert(T::TOTAL <= kLdsBytes, "LDS budget");
     __shared__ __attribute__((aligned(1024))) uint8_t smem[T::TOTAL];
 
     const int tid = threadIdx.x, lane = tid & 63, l = lane & (FT - 1), g = lane / FT;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n0 = blockIdx.x * FT, m0 = blockIdx.y * FT * MB;
+    const int n0 = blockIdx.x * FT * NB, m0 = blockIdx.y * FT * MB;
     const int wpr = (C + 31) >> 5;
     const int nblk = (C + BK - 1) / BK;
     uint8_t* as = smem + wave * T::AW;
 
     // rows past R, L and r repeat the last one that exists (outputs of the
     // former are not stored, ranks past r are zero in both rank operands)
-    const int nl = min(l, R - 1 - n0);
+    int nl[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) nl[nb] = min(FT * nb + l, R - 1 - n0);
     const uint16_t* Wt = W + (int64_t)n0 * C;
     const uint32_t* Mt = Mp + (int64_t)n0 * wpr;
     const uint16_t* Xt = X + (int64_t)m0 * C;
-    const uint32_t offW = (uint32_t)(nl * C + 8 * g);
-    const uint32_t offM = (uint32_t)(nl * wpr);
-    uint32_t offX[MB], offA[2 * RK];
+    uint32_t offW[NB], offM[NB], offX[MB], offA[2 * RK];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        offW[nb] = (uint32_t)(nl[nb] * C + 8 * g);
+        offM[nb] = (uint32_t)(nl[nb] * wpr);
+    }
 #pragma unroll
     for (int b = 0; b < MB; ++b) offX[b] = (uint32_t)(min(FT * b + l, L - 1 - m0) * C + 8 * g);
     const int arow = lane >> 3, achunk = lane & 7;
@@ -98,8 +103,8 @@ __global__ __launch_bounds__((64 * Cfg<FT, RK, MB>::NW), (Cfg<FT, RK, MB>::EU)) 
     for (int q = 0; q < 2 * RK; ++q) offA[q] = (uint32_t)(min(8 * q + arow, r - 1) * C + 8 * achunk);
 
     struct Block {
-        u32x4 w[WV], a[2 * RK], x[MB][WV];
-        uint32_t m[2];
+        u32x4 w[NB][WV], a[2 * RK], x[MB][WV];
+        uint32_t m[NB][2];
     };
     auto load_x = [&](Block& t, int k0) {
 #pragma unroll
@@ -114,12 +119,15 @@ __global__ __launch_bounds__((64 * Cfg<FT, RK, MB>::NW), (Cfg<FT, RK, MB>::EU)) 
     auto load = [&](Block& t, int blk) {
         const int k0 = blk * BK;
 #pragma unroll
-        for (int c = 0; c < WV; ++c) {
-            const bool in = !KRAG || k0 + 8 * G * c + 8 * g < C;
-            t.w[c] = *(const u32x4*)(Wt + (in ? offW + k0 + 8 * G * c : offW - 8 * g));
+        for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+            for (int c = 0; c < WV; ++c) {
+                const bool in = !KRAG || k0 + 8 * G * c + 8 * g < C;
+                t.w[nb][c] = *(const u32x4*)(Wt + (in ? offW[nb] + k0 + 8 * G * c : offW[nb] - 8 * g));
+            }
+            t.m[nb][0] = Mt[offM[nb] + 2 * blk];
+            t.m[nb][1] = Mt[offM[nb] + (KRAG ? min(2 * blk + 1, wpr - 1) : 2 * blk + 1)];
         }
-        t.m[0] = Mt[offM + 2 * blk];
-        t.m[1] = Mt[offM + (KRAG ? min(2 * blk + 1, wpr - 1) : 2 * blk + 1)];
 #pragma unroll
         for (int q = 0; q < 2 * RK; ++q) {
             const bool in = !KRAG || k0 + 8 * achunk < C;
@@ -135,20 +143,21 @@ __global__ __launch_bounds__((64 * Cfg<FT, RK, MB>::NW), (Cfg<FT, RK, MB>::EU)) 
     if (tid < 16) *(u32x2*)(smem + T::LUT + 8 * tid) = two_four ? select_lut16_entry<true>((uint32_t)tid)
                                                             : select_lut16_entry<false>((uint32_t)tid);
     for (int e = lane; e < T::AW / 16; e += 64) *(u32x4*)(as + 16 * e) = zero_u32x4();  // ranks past r stay zero
-    bf16x8 bfr[RC];  // B[n][RM c + 8g .. +7]
+    bf16x8 bfr[NB][RC];  // B[n][RM c + 8g .. +7]
     const bool b_vec = (r & 7) == 0;
 #pragma unroll
-    for (int c = 0; c < RC; ++c) {
+    for (int i = 0; i < NB * RC; ++i) {
+        const int nb = i / RC, c = i % RC;
         u32x4 v = zero_u32x4();
         const int j0 = T::RM * c + 8 * g;
-        const uint16_t* src = Bm + (int64_t)(n0 + nl) * r + j0;
+        const uint16_t* src = Bm + (int64_t)(n0 + nl[nb]) * r + j0;
         if (b_vec) {
             if (j0 < r) v = *(const u32x4*)src;
         } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e >> 1] |= (j0 + e < r ? (uint32_t)src[e] : 0u) << ((e & 1) * 16);
         }
-        bfr[c] = as_bf16x8(v);
+        bfr[nb][c] = as_bf16x8(v);
     }
 
     // The A^T operand by transpose loads (16 lanes read 4 ranks x 16 k): rank
@@ -172,11 +181,11 @@ __global__ __launch_bounds__((64 * Cfg<FT, RK, MB>::NW), (Cfg<FT, RK, MB>::EU)) 
         if constexpr (FT == 32) return mfma_32x32x16(a, b, c);
         else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
     };
-    Acc acc[MB];
+    Acc acc[NB][MB];
 #pragma unroll
-    for (int b = 0; b < MB; ++b)
+    for (int i = 0; i < NB * MB; ++i)
 #pragma unroll
-        for (int v = 0; v < NV; ++v) acc[b][v] = 0.f;
+        for (int v = 0; v < NV; ++v) acc[i / MB][i % MB][v] = 0.f;
     lds_barrier();  // the select table
 
     for (int base = wave; base < nblk; base += SLOTS * NW) {
@@ -194,7 +203,8 @@ __global__ __launch_bounds__((64 * Cfg<FT, RK, MB>::NW), (Cfg<FT, RK, MB>::EU)) 
             if (ahead < nblk) load(ring[(i + SLOTS - 1) % SLOTS], ahead);
             asm volatile("" ::: "memory");  // one wave's LDS operations complete in order
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
+            for (int i2 = 0; i2 < 2 * NB; ++i2) {
+                const int kb = i2 / NB, nb = i2 % NB;
                 // rank products of k 32kb .. +31, in the register order of the main operand
                 float tt[NV == 16 ? 16 : 8];
 #pragma unroll
@@ -206,23 +216,23 @@ __global__ __launch_bounds__((64 * Cfg<FT, RK, MB>::NW), (Cfg<FT, RK, MB>::EU)) 
                     for (int c = 0; c < RC; ++c)
                         p = mfma(frag_from_tr(lds_tr_read(as + offAt[t][0] + T::RM * kRow64 * c),
                                               lds_tr_read(as + offAt[t][1] + T::RM * kRow64 * c)),
-                                 bfr[c], p);
+                                 bfr[nb][c], p);
 #pragma unroll
                     for (int v = 0; v < NV; ++v) tt[(FT == 32 ? 0 : 4 * (t & 1)) + v] = p[v];
                 }
 #pragma unroll
                 for (int cp = 0; cp < WV / 2; ++cp) {
                     const int c = kb * WV / 2 + cp;
-                    const u32x4 sel = read_sel16(smem + T::LUT, cur.m[kb], 8 * (G * cp + g));
+                    const u32x4 sel = read_sel16(smem + T::LUT, cur.m[nb][kb], 8 * (G * cp + g));
                     const bool in = !KRAG || blk * BK + 8 * G * c + 8 * g < C;
                     u32x4 wf;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        wf[q] = merge_pair(cur.w[c][q], tt[8 * cp + 2 * q], tt[8 * cp + 2 * q + 1], s, sel[q]);
+                        wf[q] = merge_pair(cur.w[nb][c][q], tt[8 * cp + 2 * q], tt[8 * cp + 2 * q + 1], s, sel[q]);
                         if (!in) wf[q] = 0u;
                     }
 #pragma unroll
-                    for (int b = 0; b < MB; ++b) acc[b] = mfma(as_bf16x8(cur.x[b][c]), as_bf16x8(wf), acc[b]);
+                    for (int b = 0; b < MB; ++b) acc[nb][b] = mfma(as_bf16x8(cur.x[b][c]), as_bf16x8(wf), acc[nb][b]);
                 }
             }
             asm volatile("" ::: "memory");
@@ -233,19 +243,20 @@ __global__ __launch_bounds__((64 * Cfg<FT, RK, MB>::NW), (Cfg<FT, RK, MB>::EU)) 
     // token row and eight features
     __syncthreads();
     float* red = (float*)smem;
+    constexpr int NI = NB * MB;  // accumulator tiles of a wave: feature block i / MB, token block i % MB
 #pragma unroll
-    for (int b = 0; b < MB; ++b)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int v = 0; v < NV; ++v) red[((wave * MB + b) * NV + v) * 64 + lane] = acc[b][v];
+        for (int v = 0; v < NV; ++v) red[((wave * NI + i) * NV + v) * 64 + lane] = acc[i / MB][i % MB][v];
     __syncthreads();
-    for (int it = tid; it < MB * FT * FT / 8; it += 64 * NW) {
-        const int f8 = it % (FT / 8), row = it / (FT / 8) % FT, b = it / (FT * FT / 8);
+    for (int it = tid; it < NI * FT * FT / 8; it += 64 * NW) {
+        const int f8 = it % (FT / 8), row = it / (FT / 8) % FT, i = it / (FT * FT / 8);
         // accumulator element v of lane group gg is token row 4G(v/4) + 4gg + v%4
         const int v = 4 * (row / (4 * G)) + (row & 3), gg = (row >> 2) % G;
         float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
         for (int w = 0; w < NW; ++w) {
-            const f32x4* p = (const f32x4*)(red + ((w * MB + b) * NV + v) * 64 + FT * gg + 8 * f8);
+            const f32x4* p = (const f32x4*)(red + ((w * NI + i) * NV + v) * 64 + FT * gg + 8 * f8);
             const f32x4 lo = p[0], hi = p[1];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -253,20 +264,20 @@ __global__ __launch_bounds__((64 * Cfg<FT, RK, MB>::NW), (Cfg<FT, RK, MB>::EU)) 
                 sum[4 + e] += hi[e];
             }
         }
-        store8(sum, m0 + FT * b + row, n0 + 8 * f8, L, R, bias, Y);
+        store8(sum, m0 + FT * (i % MB) + row, n0 + FT * (i / MB) + 8 * f8, L, R, bias, Y);
     }
 }
 
-template <int FT, int RK, int MB>
+template <int FT, int RK, int MB, int NB = 1>
 hipError_t launch(const LayerArgs& a, hipStream_t st) {
-    const dim3 grid((unsigned)((a.R + FT - 1) / FT), (unsigned)((a.L + FT * MB - 1) / (FT * MB)));
+    const dim3 grid((unsigned)((a.R + FT * NB - 1) / (FT * NB)), (unsigned)((a.L + FT * MB - 1) / (FT * MB)));
     auto run = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(64 * Cfg<FT, RK, MB>::NW), 0, st, (const uint16_t*)a.X, (const uint16_t*)a.W, a.M,
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * Cfg<FT, RK, MB, NB>::NW), 0, st, (const uint16_t*)a.X, (const uint16_t*)a.W, a.M,
                            (const uint16_t*)a.B, (const uint16_t*)a.A, (const uint16_t*)a.bias, (uint16_t*)a.Y,
                            (int)a.L, (int)a.R, (int)a.C, (int)a.r, a.scale, (int)a.two_four);
     };
-    if (a.C % BK != 0) run(fwd_few_kernel<FT, RK, true, MB>);
-    else run(fwd_few_kernel<FT, RK, false, MB>);
+    if (a.C % BK != 0) run(fwd_few_kernel<FT, RK, true, MB, NB>);
+    else run(fwd_few_kernel<FT, RK, false, MB, NB>);
     return hipGetLastError();
 }
 
@@ -278,6 +289,12 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st) {
     if (a.L <= 16 && g16 <= 256) return launch<16, RK, 1>(a, st);
     if (a.L <= 32 && g16 <= 256) return launch<16, RK, 2>(a, st);
     if (g16 * ((a.L + 63) / 64) <= 256) return launch<16, RK, 4>(a, st);
+    // two 32-feature blocks per wave once one block each is more than a
+    // workgroup per CU: X and A are read half as often (14336 x 4096, rank 16,
+    // 32 tokens: 40.7 us against 47.1; 8192 x 4096, where it leaves half of the
+    // CUs idle, 33.1 against 22.6); above rank 32 the registers do not hold it
+    if constexpr (RK <= 2)
+        if (a.L <= 32 && g16 > 512) return launch<32, RK, 1, 2>(a, st);
     return a.L <= 32 ? launch<32, RK, 1>(a, st) : launch<32, RK, 2>(a, st);
 }
 

@@ -85,6 +85,7 @@ def test_edges(R, C, L, r, mask, scale):
     (256, 1096, 130, 128, "magnitude", 2.0),
     (8200, 328, 9, 12, "2:4", 2.0),
     (8232, 640, 31, 64, "magnitude", 1.0),
+    (8264, 1152, 20, 32, "magnitude", 2.0),
     (8192, 72, 32, 128, "magnitude", 2.0),
     (8192, 192, 65, 16, "magnitude", 2.0),
 ])
