@@ -54,7 +54,6 @@ constexpr int NT = 256;
 constexpr int BM = 256;   // tokens per tile
 constexpr int BN = 256;   // output features per whole tile (64 per wave)
 constexpr int BK = 64;    // input features per K-step
-constexpr int GROUP_M = 4;
 constexpr int kEarly = 12;  // copies of a stage issued right after the barrier; the rest a sub-step later
 
 // TM: tokens per tile, NF: 32-feature blocks per wave -- BM and 2 for a whole
@@ -133,12 +132,14 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
     int64_t m0;
     int n0;
     if constexpr (TM == BM && NF == 2) {
-        work_coords(blockIdx.x, tiles_m, tiles_n, GROUP_M, n_full, split, (C + BK - 1) / BK, tm, tn, kbeg, nk);
+        work_coords(blockIdx.x, tiles_m, tiles_n, group_rows(tiles_m * tiles_n), n_full, split, (C + BK - 1) / BK, tm,
+                    tn, kbeg, nk);
         m0 = (int64_t)tm * BM;
         n0 = tn * BN;
     } else {
         int u;
-        thin_coords(blockIdx.x, tiles_m, tiles_n, GROUP_M, n_full, split, (SPAN / TM) * (2 / NF), tm, tn, u);
+        thin_coords(blockIdx.x, tiles_m, tiles_n, group_rows(tiles_m * tiles_n), n_full, split, (SPAN / TM) * (2 / NF),
+                    tm, tn, u);
         kbeg = 0;
         nk = (C + BK - 1) / BK;
         m0 = (int64_t)tm * SPAN + (int64_t)(u % (SPAN / TM)) * TM;
@@ -615,7 +616,7 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && tp.tm > 0) e = launch_fwd_thin_bf16(a, st, tp.n_full, tp.tail, tp.tm);
     if (e == hipSuccess && sp.split > 1)
-        e = launch_split_reduce_bf16(part, sp.n_full, sp.split, tiles_m, tiles_n, GROUP_M, a.L, (int)a.R, a.bias,
+        e = launch_split_reduce_bf16(part, sp.n_full, sp.split, tiles_m, tiles_n, group_rows(tiles), a.L, (int)a.R, a.bias,
                                      a.Y, st);
     return e;
 }

@@ -30,7 +30,6 @@ constexpr int BK = 64;   // tokens per K-step
 constexpr int TILEB = BK * kRowBytes;  // 32 KiB: one operand slab
 constexpr int STAGEB = 2 * TILEB;      // dY slab + X slab
 constexpr int SMEM = 2 * STAGEB;       // two stages
-constexpr int GROUP_M = 4;
 constexpr int LOADS = TILEB / 1024 / (NT / kWave);  // 1 KiB copies per wave per slab (8)
 // copy pairs of a stage issued right after the barrier; the rest go out a
 // sub-step later (a wave stalls on a burst of asynchronous copies)
@@ -84,7 +83,8 @@ __global__ __launch_bounds__(NT, 1) void g_kernel(
     // contributions add up in dB and dA like those of different tiles
     int tm, tn;
     int kbeg, nk32;
-    work_coords(blockIdx.x, tiles_m, tiles_n, GROUP_M, n_full, split, (int)((L + BK - 1) / BK), tm, tn, kbeg, nk32);
+    work_coords(blockIdx.x, tiles_m, tiles_n, group_rows(tiles_m * tiles_n), n_full, split, (int)((L + BK - 1) / BK), tm,
+                tn, kbeg, nk32);
     const int64_t nk = nk32;
     const int i0 = tm * BM;
     const int j0 = tn * BN;
