@@ -140,7 +140,8 @@ def forward(X: torch.Tensor, W: torch.Tensor, M: torch.Tensor, B: torch.Tensor, 
     X2 = _rows(X)
     dev = _dev(X2, W, M, B, A, bias)
     R = W.shape[0]
-    if out is None:
+    fresh = out is None
+    if fresh:
         out = torch.empty((X2.shape[0], R), dtype=W.dtype, device=dev)
     flags = (_lib.FLAG_FWD_SPARSE_MFMA if sparse_mfma else 0) | (_lib.FLAG_SPLIT_LAST_WAVE if split_last_wave else 0)
     p = _problem(X2, W, B, mask_format, scale, flags=flags)
@@ -148,7 +149,7 @@ def forward(X: torch.Tensor, W: torch.Tensor, M: torch.Tensor, B: torch.Tensor, 
     ws = torch.empty(need, dtype=torch.uint8, device=dev) if need else None
     _call(dev, "lors_forward", _lib.forward, p, _ptr(X2), _ptr(W), _ptr(M), _ptr(B), _ptr(A), _ptr(bias), _ptr(out),
           _ptr(ws), need)
-    return out if X2 is X and out.dim() == 2 else out.view(*X.shape[:-1], R)
+    return out if fresh and X2 is X else out.view(*X.shape[:-1], R)
 
 
 def workspace_bytes(W: torch.Tensor, B: torch.Tensor, L: int, mask_format=BITMAP, ste: bool = False) -> int:
@@ -194,7 +195,7 @@ def backward(dY: torch.Tensor, X: torch.Tensor, W: torch.Tensor, M: torch.Tensor
     wsb = workspace.numel() if workspace is not None else 0
     _call(dev, "lors_backward", _lib.backward, p, _ptr(dY2), _ptr(X2), _ptr(W), _ptr(M), _ptr(B), _ptr(A), _ptr(dX),
           _ptr(dB), _ptr(dA), _ptr(dbias), _ptr(workspace), wsb)
-    if dX is not None and not (X2 is X and dX.dim() == 2):
+    if dX is not None and not (X2 is X and out is None):
         dX = dX.view(*X.shape)
     return dX, dB, dA, dbias
 
