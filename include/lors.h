@@ -37,6 +37,10 @@
  * rounded once to bf16 (nearest-even) before the main product; all products
  * accumulate in fp32; Y and dX are rounded to bf16 (nearest-even); G is
  * rounded to bf16 before the two rank-r products; dA, dB, dbias stay fp32.
+ * For a scale that is a power of two, on shapes of whole tiles (see
+ * LORS_FLAG_SPLIT_LAST_WAVE) the forward multiplies s.B, and dX s.A, as bf16
+ * values: exact unless they leave bf16's range.  Every other call applies s to
+ * the fp32 product.
  * The fp32 dtype keeps every intermediate in fp32 (a debug/reference path).
  *
  * Ownership: the caller owns every buffer.  The library never allocates

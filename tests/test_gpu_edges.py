@@ -203,3 +203,30 @@ def test_transposed_mask(R, C, mask):
     for k, got, want in (("dB", dB, rdB), ("dA", dA, rdA)):
         err, at = worst_tile(dev_to_f64(got), want, (8, 8))
         assert err <= TOL["bf16"], f"{k} block {at}: rel err {err:.3e}"
+
+
+# Shapes with an edge form W + s.B.A with s outside the bf16 operands, whatever
+# the scale: here s.B (or s.A) is past bf16's largest number, s.B.A is not.
+# Thin tiles in both directions, then whole tiles of the forward and of dX.
+@pytest.mark.parametrize("R,C,L", [(576, 576, 2056), (2112, 64, 4168), (64, 2112, 4168)])
+@pytest.mark.parametrize("large", ["B", "A"])
+def test_edge_tiles_keep_the_scale_out_of_bf16(R, C, L, large):
+    s, r, rng = 4.0, 8, np.random.default_rng(L + R)
+    f = lambda *shape: rng.standard_normal(shape).astype(np.float32)
+    u = lambda *shape: (rng.uniform(1, 1.9, shape) * rng.choice([-1, 1], shape)).astype(np.float32)
+    up, down = np.float32(2.0 ** 126), np.float32(2.0 ** -126)
+    Bv, Av = u(R, r) * (up if large == "B" else down), u(r, C) * (down if large == "B" else up)
+    Mk = (rng.random((R, C)) < 0.5).astype(np.uint8)
+    X, W, B, A, dY = (synth.f32_to_bf16_bits(v) for v in (f(L, C), f(R, C) * Mk, Bv, Av, f(L, R)))
+    Xt, Wt, Bt, At, dYt = (to_dev(t, "bf16") for t in (X, W, B, A, dY))
+    M = ops.mask_pack(torch.from_numpy(Mk).cuda(), ops.BITMAP)
+    print("scale outside", (R, C, L, large), flush=True)
+    Y = ops.forward(Xt, Wt, M, Bt, At, s)
+    dX = ops.backward(dYt, Xt, Wt, M, Bt, At, s)[0]  # (dB and dA do leave their range)
+    x, w, b, a, dy = (to_f64(t, "bf16") for t in (X, W, B, A, dY))
+    Wm = np.where(Mk, w + s * (b @ a), 0.0)
+    for k, got, want in (("Y", Y, x @ Wm.T), ("dX", dX, dy @ Wm)):
+        got = dev_to_f64(got)
+        assert np.all(np.isfinite(got)), f"{k}: not finite"
+        err, at = worst_tile(got, want, (64, 64))
+        assert err <= TOL["bf16"], f"{k} block {at}: rel err {err:.3e}"
