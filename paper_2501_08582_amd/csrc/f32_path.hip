@@ -104,7 +104,8 @@ __global__ __launch_bounds__(NT) void fwd_f32(const float* __restrict__ X, const
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const uint32_t keep = keep_nibble(word, 2 * j + h, two_four);
+            // nothing is kept past C, where a 2:4 word's codes (0) name position 0
+            const uint32_t keep = k0 + 8 * j + 4 * h < C ? keep_nibble(word, 2 * j + h, two_four) : 0u;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 acc = mfma2(x[j][e], (keep >> e) & 1u ? fmaf(s, ba[4 * j + e], w[j][e]) : 0.f, acc);
@@ -171,7 +172,8 @@ __global__ __launch_bounds__(NT) void dx_f32(const float* __restrict__ dY, const
         }
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const uint32_t keep = keep_nibble(word[v], l >> 2, two_four) >> (l & 3);
+            // (nothing is kept past R, whose 2:4 words read as 0)
+            const uint32_t keep = k0 + 8 * (v >> 2) + 4 * h < R ? keep_nibble(word[v], l >> 2, two_four) >> (l & 3) : 0u;
             acc = mfma2(d[v >> 2][v & 3], keep & 1u ? fmaf(s, ba[v], w[v]) : 0.f, acc);
         }
     }

@@ -230,3 +230,29 @@ def test_edge_tiles_keep_the_scale_out_of_bf16(R, C, L, large):
         assert np.all(np.isfinite(got)), f"{k}: not finite"
         err, at = worst_tile(got, want, (64, 64))
         assert err <= TOL["bf16"], f"{k} block {at}: rel err {err:.3e}"
+
+
+@pytest.mark.parametrize("fmt", [ops.BITMAP, ops.TWO_FOUR])
+@pytest.mark.parametrize("R,C", [(36, 36), (100, 68), (68, 300)])
+def test_fp32_blocks_past_the_tensors_keep_nothing(R, C, fmt):
+    """R and C end inside a 32-wide k block.  A column of A that is not finite
+    and that the mask drops from every row leaves dX exactly 0 there, and an
+    infinite row of B gives Y an infinity: no NaN comes from the block's end."""
+    L, r = 40, 8
+    rng = np.random.default_rng(R + C)
+    Mk = np.tile(np.array([0, 1, 1, 0], np.uint8), (R, C // 4))  # drops every column n with n % 4 in (0, 3)
+    f = lambda *shape: np.abs(rng.standard_normal(shape)).astype(np.float32) + np.float32(0.1)
+    X, W, B, A, dY = f(L, C), f(R, C) * Mk, f(R, r), f(r, C), f(L, R)
+    M = ops.mask_pack(torch.from_numpy(Mk).cuda(), fmt)
+    Xt, Wt, dYt = (to_dev(t, "f32") for t in (X, W, dY))
+    Ainf = A.copy()
+    Ainf[0, 0::4], Ainf[1, 3::4] = np.inf, np.nan
+    dX = dev_to_f64(ops.backward(dYt, Xt, Wt, M, to_dev(B, "f32"), to_dev(Ainf, "f32"), 1.5, fmt)[0])
+    assert np.all(dX[:, 0::4] == 0) and np.all(dX[:, 3::4] == 0)
+    ref = olors.backward(*(np.asarray(t, np.float64) for t in (dY, X, W)), Mk, B.astype(np.float64),
+                         A.astype(np.float64), 1.5)[0]
+    assert worst_tile(dX, ref, (32, 32))[0] <= TOL["f32"]
+    Binf = B.copy()
+    Binf[R - 1, 2] = np.inf
+    Y = dev_to_f64(ops.forward(Xt, Wt, M, to_dev(Binf, "f32"), to_dev(A, "f32"), 1.5, fmt))
+    assert np.all(Y[:, R - 1] == np.inf) and np.all(np.isfinite(Y[:, :R - 1]))
