@@ -106,7 +106,8 @@ __device__ __forceinline__ u32x4 select_lut_entry(uint32_t b) {
 }
 
 // Half of a select entry: the two words for four consecutive elements whose
-// keep bits are the nibble n (for the 2:4 layout: whose group code is n).
+// keep bits are the nibble n (for the 2:4 layout: whose group code is n; no
+// group has code 0, which fills words past the contraction: it keeps nothing).
 // The sixteen half entries make a 128-byte table; it spans distinct LDS
 // banks, so lanes reading it with arbitrary nibbles never conflict (a lane
 // group reading the 256-entry table of whole entries does, about 3.6-way on
@@ -114,7 +115,7 @@ __device__ __forceinline__ u32x4 select_lut_entry(uint32_t b) {
 template <bool TWO_FOUR>
 __device__ __forceinline__ u32x2 select_lut16_entry(uint32_t n) {
     uint32_t keep = n;
-    if constexpr (TWO_FOUR) keep = (1u << (n & 3u)) | (1u << (n >> 2));
+    if constexpr (TWO_FOUR) keep = n == 0 ? 0u : (1u << (n & 3u)) | (1u << (n >> 2));
     u32x2 e;
 #pragma unroll
     for (int p = 0; p < 2; ++p)

@@ -256,3 +256,21 @@ def test_fp32_blocks_past_the_tensors_keep_nothing(R, C, fmt):
     Binf[R - 1, 2] = np.inf
     Y = dev_to_f64(ops.forward(Xt, Wt, M, to_dev(Binf, "f32"), to_dev(A, "f32"), 1.5, fmt))
     assert np.all(Y[:, R - 1] == np.inf) and np.all(np.isfinite(Y[:, :R - 1]))
+
+
+# tile forward: a last K-step that ends past C, as thin tiles and as whole ones;
+# few tokens
+@pytest.mark.parametrize("R,L", [(520, 2056), (2112, 4168), (520, 40)])
+@pytest.mark.parametrize("fmt", [ops.BITMAP, ops.TWO_FOUR])
+def test_columns_past_the_contraction_keep_nothing(R, L, fmt):
+    """An infinite row of B gives Y an infinity: no NaN comes from the columns
+    past C of the last K-step."""
+    C, r = 72, 8
+    rng = np.random.default_rng(R + L)
+    Mk = np.tile(np.array([0, 1, 1, 0], np.uint8), (R, C // 4))
+    f = lambda *shape: np.abs(rng.standard_normal(shape)).astype(np.float32) + np.float32(0.1)
+    B = f(R, r)
+    B[R - 1, 2] = np.inf
+    X, W, B, A = (to_dev(synth.f32_to_bf16_bits(v), "bf16") for v in (f(L, C), f(R, C) * Mk, B, f(r, C)))
+    Y = ops.forward(X, W, ops.mask_pack(torch.from_numpy(Mk).cuda(), fmt), B, A, 1.5, fmt)
+    assert torch.all(Y[:, R - 1] == float("inf")) and torch.isfinite(Y[:, :R - 1]).all()
