@@ -147,8 +147,9 @@ typedef enum lors_mask_format {
  * every tile of the short wave, fewer pieces are used, or none (the call
  * then runs as without the flag).  lors_workspace_bytes accounts for the
  * partials, and lors_forward requires a workspace when there are any.  No
- * effect for fp32; applies to ranks up to 64 (above, every tile runs as thin
- * tiles).  The weight gradient always splits such a wave, with no
+ * effect for fp32 or on a forward of few tokens (at most 32, or at most one
+ * 64-token, 32-feature block per CU: it has no tiles to cut); applies to ranks
+ * up to 64 (above, every tile runs as thin tiles).  The weight gradient always splits such a wave, with no
  * workspace: its pieces' partial G tiles go through the same rank-r products
  * and atomics as whole tiles. */
 #define LORS_FLAG_SPLIT_LAST_WAVE 0x8u

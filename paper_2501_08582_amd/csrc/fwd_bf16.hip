@@ -669,21 +669,9 @@ hipError_t launch_thin_rk(const LayerArgs& a, hipStream_t st, int first, int tai
 
 #ifndef LORS_THIN_TILES
 
-// Whether the forward takes the kernel for few tokens: up to 32 tokens always
-// (there it is one read of W), more while its 32-feature, 64-token workgroups
-// number at most one per CU; beyond that the thin tiles, which form W' once
-// per 64 to 256 tokens of 128 features, are faster.  Measured, thin against
-// few (us): 4096 x 4096, rank 16, 1 / 64 / 128 tokens 42 / 42 / 43 against 13 /
-// 25 / 30, 256 tokens 43 against 45; 14336 x 4096, 32 / 64 tokens 53 / 55
-// against 44 / 62; 4096 x 14336, rank 64, 64 / 128 tokens 172 / 170 against
-// 104 / 123.  (The bound on C keeps its 32-bit offsets of 128 rows.)
-static bool few_tokens(const LayerArgs& a) {
-    return a.C <= (1 << 24) && (a.L <= 32 || ((a.R + 31) / 32) * ((a.L + 63) / 64) <= 256);
-}
-
 hipError_t launch_fwd_bf16(const LayerArgs& a, hipStream_t st) {
     if (a.L == 0) return hipSuccess;
-    if (!a.sparse_mfma && few_tokens(a)) return launch_fwd_few_bf16(a, st);
+    if (!a.sparse_mfma && fwd_few_tokens(a.L, a.R, a.C)) return launch_fwd_few_bf16(a, st);
     switch ((a.r + 15) / 16) {
         case 1: return launch_rk<1>(a, st);
         case 2: return launch_rk<2>(a, st);

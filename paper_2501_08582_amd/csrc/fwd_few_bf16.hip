@@ -285,16 +285,16 @@ template <int RK>
 hipError_t launch_rk(const LayerArgs& a, hipStream_t st) {
     // 16 features per workgroup while that leaves at most one per CU, with
     // the smallest token block that takes all tokens
-    const int64_t g16 = (a.R + 15) / 16;
-    if (a.L <= 16 && g16 <= 256) return launch<16, RK, 1>(a, st);
-    if (a.L <= 32 && g16 <= 256) return launch<16, RK, 2>(a, st);
-    if (g16 * ((a.L + 63) / 64) <= 256) return launch<16, RK, 4>(a, st);
+    const int64_t g16 = (a.R + 15) / 16, cus = device_cus();
+    if (a.L <= 16 && g16 <= cus) return launch<16, RK, 1>(a, st);
+    if (a.L <= 32 && g16 <= cus) return launch<16, RK, 2>(a, st);
+    if (g16 * ((a.L + 63) / 64) <= cus) return launch<16, RK, 4>(a, st);
     // two 32-feature blocks per wave once one block each is more than a
     // workgroup per CU: X and A are read half as often (14336 x 4096, rank 16,
     // 32 tokens: 40.7 us against 47.1; 8192 x 4096, where it leaves half of the
     // CUs idle, 33.1 against 22.6); above rank 32 the registers do not hold it
     if constexpr (RK <= 2)
-        if (a.L <= 32 && g16 > 512) return launch<32, RK, 1, 2>(a, st);
+        if (a.L <= 32 && g16 > 2 * cus) return launch<32, RK, 1, 2>(a, st);
     return a.L <= 32 ? launch<32, RK, 1>(a, st) : launch<32, RK, 2>(a, st);
 }
 

@@ -80,6 +80,17 @@ ThinPlan thin_plan(int64_t L, int64_t N);
 // feature halves of 256 tokens; a short last wave, or a grid that is one, as
 // thin_plan's.
 int thin_only_plan(int64_t L, int64_t N, ThinPlan run[2]);
+// compute units of the current device (256 where there is none)
+int device_cus();
+// Whether the forward takes the kernel for few tokens: up to 32 tokens always
+// (there it is one read of W), more while its 32-feature, 64-token workgroups
+// number at most one per CU; beyond that the thin tiles, which form W' once
+// per 64 to 256 tokens of 128 features, are faster.  Measured, thin against
+// few (us): 4096 x 4096, rank 16, 1 / 64 / 128 tokens 42 / 42 / 43 against 13 /
+// 25 / 30, 256 tokens 43 against 45; 14336 x 4096, 32 / 64 tokens 53 / 55
+// against 44 / 62; 4096 x 14336, rank 64, 64 / 128 tokens 172 / 170 against
+// 104 / 123.  (The bound on C keeps its 32-bit offsets of 128 rows.)
+bool fwd_few_tokens(int64_t L, int64_t R, int64_t C);
 // Shapes of whole tiles, which never split over K: 256 x 256 tiles and 64-wide
 // K-steps cover the forward's L x R, K = C (dX's L x C, K = R) exactly.
 inline bool fwd_whole_tiles(int64_t L, int64_t R, int64_t C) {

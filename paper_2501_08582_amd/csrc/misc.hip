@@ -397,7 +397,7 @@ hipError_t launch_split_reduce_bf16(const float* part, int n_full, int split, in
 
 // compute units of the current device, read once per device (calls from
 // several host threads may both read it; they store the same value)
-static int device_cus() {
+int device_cus() {
     static std::atomic<int> cus_of[64];
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) {
@@ -407,6 +407,10 @@ static int device_cus() {
         if (n > 0) cus = n;
     }
     return cus;
+}
+
+bool fwd_few_tokens(int64_t L, int64_t R, int64_t C) {
+    return C <= (1 << 24) && (L <= 32 || ((R + 31) / 32) * ((L + 63) / 64) <= device_cus());
 }
 
 TailSplit tail_split(int64_t tiles, int64_t nk, int64_t max_part_bytes) {

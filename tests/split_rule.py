@@ -31,6 +31,11 @@ def split_bytes(tiles, nk, budget, cus=256):
     return (tiles % cus) * s * 256 * 256 * 4 if s > 1 else 0
 
 
+def group_rows(tiles, cus=256):
+    """Tile rows the forward walks at a time (dX: always 4)."""
+    return 8 if tiles > cus else 4
+
+
 def split_tiles(rows, cols, cus=256, group_m=4):
     """(row0, col0) of the output tiles that run in pieces, given that the
     grid splits: the logical tiles past the whole waves, mapped to tiles in
@@ -47,6 +52,12 @@ def split_tiles(rows, cols, cus=256, group_m=4):
         within = t - g * per_group
         out.append((256 * (first + within % gsz), 256 * (within // gsz)))
     return out
+
+
+def few_tokens(L, R, C, cus=256):
+    """The forward's kernel for few tokens, which never splits: at most 32
+    tokens, or at most one 64-token, 32-feature workgroup per CU."""
+    return C <= 1 << 24 and (L <= 32 or -(-R // 32) * -(-L // 64) <= cus)
 
 
 def fwd_whole_tiles(L, R, C):

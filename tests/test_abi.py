@@ -296,6 +296,8 @@ def test_no_weak_symbol_defined_twice():
 
 from split_rule import dx_whole_tiles as _dx_whole  # noqa: E402
 from split_rule import fwd_whole_tiles as _fwd_whole  # noqa: E402
+from split_rule import few_tokens as _few_tokens  # noqa: E402
+from split_rule import pieces as _split_pieces  # noqa: E402
 from split_rule import split_budget as _split_budget  # noqa: E402
 from split_rule import split_bytes as _tail_split_bytes  # noqa: E402
 
@@ -308,12 +310,12 @@ def test_workspace_query_split_last_wave(lib):
                        (8192, 65536, 4300, 16), (32768, 16384, 4300, 16), (5120, 5120, 4000, 64),
                        # the GPU split tests' shapes
                        (65792, 1024, 300, 16), (1024, 65792, 250, 64), (1024, 65792, 200, 5),
-                       (1024, 65792, 256, 100)]:
+                       (1024, 65792, 256, 100), (65792, 2048, 200, 64), (7400, 3016, 2280, 32)]:
         base = _lib.workspace_bytes(_p(R=R, C=C, L=L, r=r))
         tl = -(-L // 256)
         budget = _split_budget(R, C, r)
         fwd = dx = 0
-        if r <= 64 and not _fwd_whole(L, R, C):
+        if r <= 64 and not _fwd_whole(L, R, C) and not _few_tokens(L, R, C):
             fwd = _tail_split_bytes(tl * -(-R // 256), -(-C // 64), budget)
         if -(-r // 8) * 8 <= 64 and not _dx_whole(L, R, C):
             dx = _tail_split_bytes(tl * -(-C // 256), -(-R // 64), budget)
@@ -336,6 +338,14 @@ def test_workspace_query_split_last_wave(lib):
     # the CUs
     assert _lib.workspace_bytes(_p(R=32768, C=16384, L=4300, r=16, flags=F)) - \
         _lib.workspace_bytes(_p(R=32768, C=16384, L=4300, r=16)) == 48 << 20
+    # few tokens: 256 x 65536 at 200 tokens is one forward tile, which 7 pieces
+    # would fit, but the kernel for few tokens has no tiles (dX: whole waves)
+    assert _few_tokens(200, 256, 65536) and not _dx_whole(200, 256, 65536)
+    assert _lib.workspace_bytes(_p(R=256, C=65536, L=200, r=16, flags=F)) == \
+        _lib.workspace_bytes(_p(R=256, C=65536, L=200, r=16))
+    # 65792 x 2048 at 200 tokens is past that kernel: 257 forward tiles, the
+    # last in 8 pieces
+    assert not _few_tokens(200, 65792, 2048) and _split_pieces(257, 32, _split_budget(65792, 2048, 64)) == 8
     # no effect for fp32, and none without tokens
     assert _lib.workspace_bytes(_p(dtype=_lib.DTYPE_F32, flags=F)) == 0
     assert _lib.workspace_bytes(_p(L=0, flags=F)) == _lib.workspace_bytes(_p(L=0))

@@ -317,7 +317,7 @@ def test_no_merged_weight_allocation():
     assert torch.cuda.max_memory_allocated() - base == 0
 
 
-@pytest.mark.parametrize("R,C,L,r", [(1024, 65792, 200, 5),     # forward and dX split over K, partials
+@pytest.mark.parametrize("R,C,L,r", [(1024, 65792, 200, 5),     # dX split over K, partials
                                      (5120, 5120, 4096, 64)])    # 13B q/k/v/o: thin tiles, no partials
 def test_layer_step_allocates_nothing_and_its_scratch_stays_small(R, C, L, r):
     """The step the benchmark times (LayerStep: every call with
@@ -588,9 +588,13 @@ def test_weight_gradient_tail_split(R, C, L, r, mask):
 # the rule; test_abi checks the library against it):
 #   65792 x 1024, 300 tokens: forward 2 x 257 tiles (2 in 4 pieces), dX 2 x 4
 #     tiles (all 8 in 4 pieces);
-#   1024 x 65792, 250 or 200 tokens: forward 4 tiles in 8 pieces, dX 257
-#     tiles (1 in 4 pieces); rank 5 adds the padded copy of B; at 256 tokens
-#     (whole tiles) rank 100 runs two passes and is not split.
+#   65792 x 2048, 200 tokens: forward 257 tiles (1 in 8 pieces), dX 8 tiles in
+#     8 pieces;
+#   7400 x 3016, 2280 tokens: forward 9 x 29 tiles (5 in 2 pieces, eight tile
+#     rows at a time, K-steps that end past C), dX not (its 108 pieces do not fit);
+#   1024 x 65792, 250 or 200 tokens: dX 257 tiles (1 in 4 pieces), the forward
+#     has few tokens; rank 5 adds the padded copy of B; at 256 tokens (whole
+#     tiles) and rank 100 nothing is split.
 # Split tiles must agree with the unsplit call within one bf16 ulp (the two
 # differ only in fp32 summation order), every other tile bit for bit, and
 # both with the oracle; W is unpruned so that the split pieces also see data
@@ -606,11 +610,13 @@ def _ulp_close(a, b):
     return np.abs(a - b) <= ulp + rms / 4096
 
 
-@pytest.mark.parametrize("R,C,L,r,mask,bias", [(65792, 1024, 300, 16, "magnitude", True),
-                                               (1024, 65792, 250, 64, "2:4", False),
-                                               (1024, 65792, 200, 5, "magnitude", False),
-                                               (1024, 65792, 256, 100, "magnitude", False)])
-def test_split_last_wave(R, C, L, r, mask, bias):
+@pytest.mark.parametrize("R,C,L,r,mask,bias,splits", [(65792, 1024, 300, 16, "magnitude", True, "Y dX"),
+                                                      (65792, 2048, 200, 64, "2:4", False, "Y dX"),
+                                                      (7400, 3016, 2280, 32, "magnitude", True, "Y"),
+                                                      (1024, 65792, 250, 64, "2:4", False, "dX"),
+                                                      (1024, 65792, 200, 5, "magnitude", False, "dX"),
+                                                      (1024, 65792, 256, 100, "magnitude", False, "")])
+def test_split_last_wave(R, C, L, r, mask, bias, splits):
     import split_rule
     from gpu_helpers import unprune as _unprune
     inp = _inputs("llama2_7b_q_proj", R=R, C=C, r=r, mask=mask, seed=1500 + r, L=L)
@@ -643,8 +649,12 @@ def test_split_last_wave(R, C, L, r, mask, bias):
     for name, got, ref0, N, K, ok in (("Y", Y, Y0, R, C, r <= 64), ("dX", dX, dX0, C, R, -(-r // 8) * 8 <= 64)):
         g, u = dev_to_f64(got), dev_to_f64(ref0)
         whole = (split_rule.fwd_whole_tiles(L, R, C) if name == "Y" else split_rule.dx_whole_tiles(L, R, C))
-        split = ok and not whole and split_rule.pieces(tl * -(-N // 256), -(-K // 64), budget, cus) > 1
-        rects = split_rule.split_tiles(L, N, cus) if split else []
+        few = name == "Y" and split_rule.few_tokens(L, R, C, cus)
+        tiles = tl * -(-N // 256)
+        split = ok and not whole and not few and split_rule.pieces(tiles, -(-K // 64), budget, cus) > 1
+        assert split == (name in splits.split()), f"{name}: the shape was meant to {'' if name in splits else 'not '}split"
+        group = split_rule.group_rows(tiles, cus) if name == "Y" else 4
+        rects = split_rule.split_tiles(L, N, cus, group) if split else []
         inside = np.zeros(g.shape, dtype=bool)
         for m0, n0 in rects:
             inside[m0:m0 + 256, n0:n0 + 256] = True
@@ -667,8 +677,7 @@ def test_split_last_wave(R, C, L, r, mask, bias):
     e_da = relerr(dev_to_f64(dA)[:, cols], olors.da_cols(f(inp.dY), f(inp.X), inp.M, f(inp.B), s, cols))
     print({"split tiles checked": checked, "dB rows": e_db, "dA cols": e_da}, flush=True)
     assert e_db <= TOL[dt] and e_da <= TOL[dt]
-    if r <= 64:
-        assert checked > 0, "the shape was meant to split"
+    assert (checked > 0) == bool(splits)
 
 
 # ---------------------------------------------------------------------------
@@ -698,7 +707,8 @@ def _guards_intact(buf, n):
     (520, 776, 300, 16, "magnitude", True, False),   # ragged in every dimension
     (264, 520, 130, 112, "2:4", True, False),        # two rank passes (the second adds onto Y and dX)
     (264, 1032, 77, 5, "magnitude", False, True),    # padded B in the workspace; no split (small R*C)
-    (1024, 65792, 200, 5, "magnitude", True, True),  # split forward and dX with partials in the workspace
+    (1024, 65792, 200, 5, "magnitude", True, True),  # split dX with partials in the workspace, few-token forward
+    (7400, 3016, 2280, 5, "magnitude", True, True),  # split forward with partials in the workspace
 ])
 def test_outputs_and_workspace_stay_in_bounds(R, C, L, r, mask, bias, split):
     from paper_2501_08582_amd import _lib
