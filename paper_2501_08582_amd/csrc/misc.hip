@@ -113,7 +113,9 @@ __global__ __launch_bounds__(NT) void pack_rows_kernel(Src src, int64_t words, u
     if (w < words) out[w] = pack_word<TWO_FOUR>(mine, 8, 8 * w, first_bad);
 }
 
-// Any C: one thread per word.
+// Any C: one thread per word, in 16-byte vectors where the word is whole and
+// its row starts on one.  Byte masks of 4096 x 14352 (every row does) and 4096
+// x 14332 (one in four): 119 us by elements alone, 16.6 and 86 us so.
 template <class Src, bool TWO_FOUR>
 __global__ __launch_bounds__(NT) void pack_words_kernel(Src src, int64_t R, int C, int wpr, uint32_t* __restrict__ out,
                                                         unsigned long long* __restrict__ first_bad) {
@@ -121,8 +123,15 @@ __global__ __launch_bounds__(NT) void pack_words_kernel(Src src, int64_t R, int 
     if (t >= R * wpr) return;
     const int64_t i = t / wpr;
     const int c0 = (int)(t - i * wpr) * 32;
+    constexpr int E = Src::E;
+    const auto* at = src.p + i * C + c0;
     uint32_t f = 0;
-    for (int e = 0; e < 32 && c0 + e < C; ++e) f |= (src.kept(i * C + c0 + e) ? 1u : 0u) << e;
+    if (c0 + 32 <= C && ((uintptr_t)at & 15) == 0) {
+#pragma unroll
+        for (int q = 0; q < 32 / E; ++q) f |= src.flags(((const u32x4*)at)[q]) << (E * q);
+    } else {
+        for (int e = 0; e < 32 && c0 + e < C; ++e) f |= (src.kept(i * C + c0 + e) ? 1u : 0u) << e;
+    }
     out[t] = pack_word<TWO_FOUR>(f, C / 4 - c0 / 4, i * (C / 4) + c0 / 4, first_bad);
 }
 

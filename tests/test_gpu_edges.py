@@ -149,10 +149,12 @@ def test_fp32_edges(R, C, L, r, mask, scale):
 
 
 # mask derivation and packing: whole-word rows (vector loads, a last wave of
-# words that is not full) and rows that end inside a word
+# words that is not full) and rows that end inside a word, of which all, some
+# or one in sixteen start on a 16-byte vector
 @pytest.mark.parametrize("dtype", [torch.uint8, torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("R,C,fmt", [(1, 32, ops.BITMAP), (3, 352, ops.TWO_FOUR), (67, 96, ops.BITMAP),
-                                     (65, 1024, ops.TWO_FOUR), (5, 36, ops.TWO_FOUR), (9, 1000, ops.BITMAP)])
+                                     (65, 1024, ops.TWO_FOUR), (5, 36, ops.TWO_FOUR), (9, 1000, ops.BITMAP),
+                                     (35, 112, ops.TWO_FOUR), (7, 85, ops.BITMAP)])
 def test_mask_words(dtype, R, C, fmt):
     from oracle import masks as omasks
     rng = np.random.default_rng(R + C)
