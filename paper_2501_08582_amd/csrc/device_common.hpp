@@ -77,12 +77,26 @@ __device__ __forceinline__ int xcd_order(int bid, int n) {
     return x * (n >> 3) + min(x, n & 7) + (bid >> 3);
 }
 
-// Tile rows that the forward and the weight gradient walk at a time: 4 in a
-// grid of one wave, 8 in a longer one, whose XCDs then fetch their column panels
-// half as often (4096 x 14336, 8192 tokens, rank 64: forward 981 -> 969 us,
-// weight gradient 787 -> 771; with 8 in one wave of 4096 x 4096 both lose 0.5 %,
-// and dX loses 0.6 % at either).
-__host__ __device__ constexpr int group_rows(int64_t tiles) { return tiles > 256 ? 8 : 4; }
+// Tile rows that a grid walks at a time: 4, or 8 where the XCDs gain more from
+// fetching their column panels half as often than they lose (dX: always 4, it
+// loses 0.6 % at 8).  A wave is 256 tiles, one per CU of an undivided MI355X; the
+// order of the tiles changes no result.
+//   Forward: several waves of at most 32 tile rows.  Rank 64, 8 rows against 4
+// (us): 4096 x 14336, 8192 tokens 981 and 995; 28672 x 8192, 6144 tokens 2965 and
+// 3044.  With 64 tile rows every XCD walks the same column panels at the same
+// time: 28672 x 8192, 16384 tokens 7945 and 7620, 8192 x 8192 2263 and 2186.
+__host__ __device__ constexpr int fwd_group_rows(int64_t tiles_m, int64_t tiles_n) {
+    return tiles_m * tiles_n > 256 && tiles_m <= 32 ? 8 : 4;
+}
+//   Weight gradient: at 8 rows twice as many tiles add to the same columns of dA
+// at once, which only a long main loop (128 K-steps) on a wide G of more than
+// three waves makes up for: 4096 x 14336, rank 64, 8192 / 16384 tokens 768 / 1472
+// us against 777 / 1511 with 4 rows, but 4096 tokens 442 and 440; 4096 x 11008
+// (2.7 waves), 8192 tokens 617 and 611; 11008 x 4096, rank 128, 256 tokens 217 and
+// 195.
+__host__ __device__ constexpr int g_group_rows(int64_t tiles_m, int64_t tiles_n, int64_t nk) {
+    return tiles_m * tiles_n > 768 && nk >= 128 && 2 * tiles_n >= 5 * tiles_m ? 8 : 4;
+}
 
 // Output tile (tm, tn) of logical tile t: the logical order walks `group_m`
 // tile rows at a time, so the tiles an XCD holds at once share few operand

@@ -132,13 +132,13 @@ __global__ __launch_bounds__(NT, 1) void fwd_kernel(
     int64_t m0;
     int n0;
     if constexpr (TM == BM && NF == 2) {
-        work_coords(blockIdx.x, tiles_m, tiles_n, group_rows(tiles_m * tiles_n), n_full, split, (C + BK - 1) / BK, tm,
+        work_coords(blockIdx.x, tiles_m, tiles_n, fwd_group_rows(tiles_m, tiles_n), n_full, split, (C + BK - 1) / BK, tm,
                     tn, kbeg, nk);
         m0 = (int64_t)tm * BM;
         n0 = tn * BN;
     } else {
         int u;
-        thin_coords(blockIdx.x, tiles_m, tiles_n, group_rows(tiles_m * tiles_n), n_full, split, (SPAN / TM) * (2 / NF),
+        thin_coords(blockIdx.x, tiles_m, tiles_n, fwd_group_rows(tiles_m, tiles_n), n_full, split, (SPAN / TM) * (2 / NF),
                     tm, tn, u);
         kbeg = 0;
         nk = (C + BK - 1) / BK;
@@ -623,7 +623,7 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && tp.tm > 0) e = launch_fwd_thin_bf16(a, st, tp.n_full, tp.tail, tp.tm);
     if (e == hipSuccess && sp.split > 1)
-        e = launch_split_reduce_bf16(part, sp.n_full, sp.split, tiles_m, tiles_n, group_rows(tiles), a.L, (int)a.R, a.bias,
+        e = launch_split_reduce_bf16(part, sp.n_full, sp.split, tiles_m, tiles_n, fwd_group_rows(tiles_m, tiles_n), a.L, (int)a.R, a.bias,
                                      a.Y, st);
     return e;
 }

@@ -83,8 +83,9 @@ __global__ __launch_bounds__(NT, 1) void g_kernel(
     // contributions add up in dB and dA like those of different tiles
     int tm, tn;
     int kbeg, nk32;
-    work_coords(blockIdx.x, tiles_m, tiles_n, group_rows(tiles_m * tiles_n), n_full, split, (int)((L + BK - 1) / BK), tm,
-                tn, kbeg, nk32);
+    const int nk_all = (int)((L + BK - 1) / BK);
+    work_coords(blockIdx.x, tiles_m, tiles_n, g_group_rows(tiles_m, tiles_n, nk_all), n_full, split, nk_all, tm, tn,
+                kbeg, nk32);
     const int64_t nk = nk32;
     const int i0 = tm * BM;
     const int j0 = tn * BN;

@@ -31,9 +31,9 @@ def split_bytes(tiles, nk, budget, cus=256):
     return (tiles % cus) * s * 256 * 256 * 4 if s > 1 else 0
 
 
-def group_rows(tiles, cus=256):
+def fwd_group_rows(tiles_m, tiles_n):
     """Tile rows the forward walks at a time (dX: always 4)."""
-    return 8 if tiles > cus else 4
+    return 8 if tiles_m * tiles_n > 256 and tiles_m <= 32 else 4
 
 
 def split_tiles(rows, cols, cus=256, group_m=4):

@@ -653,7 +653,7 @@ def test_split_last_wave(R, C, L, r, mask, bias, splits):
         tiles = tl * -(-N // 256)
         split = ok and not whole and not few and split_rule.pieces(tiles, -(-K // 64), budget, cus) > 1
         assert split == (name in splits.split()), f"{name}: the shape was meant to {'' if name in splits else 'not '}split"
-        group = split_rule.group_rows(tiles, cus) if name == "Y" else 4
+        group = split_rule.fwd_group_rows(tl, -(-N // 256)) if name == "Y" else 4
         rects = split_rule.split_tiles(L, N, cus, group) if split else []
         inside = np.zeros(g.shape, dtype=bool)
         for m0, n0 in rects:
