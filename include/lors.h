@@ -178,7 +178,7 @@ typedef struct lors_problem {
 /* Human-readable name of a status code (static storage). */
 const char* lors_status_string(int status);
 
-/* ABI version: major * 10000 + minor * 100 + patch. */
+/* ABI version: major * 10000 + minor * 100 + patch (10200: lors_round_bf16). */
 int lors_version(void);
 
 /* Bytes of a packed R x C mask (either layout): 4 * R * ceil(C/32). */

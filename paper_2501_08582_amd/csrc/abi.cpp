@@ -115,7 +115,7 @@ const char* lors_status_string(int status) {
     }
 }
 
-int lors_version(void) { return 10100; }
+int lors_version(void) { return 10200; }
 
 size_t lors_mask_packed_bytes(int64_t R, int64_t C) {
     const int64_t n = (C < 0) ? -1 : bytes_of(R, words_per_row(C), 4);

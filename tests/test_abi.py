@@ -45,7 +45,7 @@ def test_status_strings(lib):
         s = _lib.string(code)
         assert s.startswith("LORS_")
     assert "unknown" in _lib.string(99)
-    assert lib.lors_version() == 10100
+    assert lib.lors_version() == 10200
 
 
 @pytest.mark.parametrize("R,C", [(1, 1), (3, 31), (3, 32), (5, 33), (4096, 14336)])
@@ -464,3 +464,23 @@ def test_noalloc_rejects_problems_beyond_its_scratch(lib):
                 continue
             p = _p(R=w.R, C=w.C, L=w.L, r=w.r, dtype=dt, mask_format=fmt, flags=flags)
             assert _lib.workspace_bytes(p) <= _lib.NOALLOC_SCRATCH_BYTES, (w.name, flags)
+
+
+def test_round_bf16_validation(lib):
+    a, ao, b, bo = _ptrs(4)
+    call = lambda *args: _lib.round_bf16(*args, None)  # noqa: E731
+    for k in (0, 2, 3, 5):  # null -> shape -> alignment -> alias, before any HIP call
+        args = [a, 64, ao, b, 64, bo]
+        args[k] = None
+        assert call(*args) == _lib.ERR_NULL
+        args[k] = [a, 64, ao, b, 64, bo][k] + 8
+        assert call(*args) == _lib.ERR_ALIGN
+        args[4 if k < 3 else 1] = -1
+        assert call(*args) == _lib.ERR_SHAPE
+    for n in (-1, (1 << 58) + 1, -(1 << 63)):
+        assert call(a, n, ao, b, 64, bo) == call(a, 64, ao, b, n, bo) == _lib.ERR_SHAPE
+    assert call(None, -1, ao, b, 64, bo) == _lib.ERR_NULL
+    for args in ((a, 64, a, b, 64, bo), (a, 64, b, b, 64, bo), (a, 64, ao, b, 64, a + 16),
+                 (a, 64, a + 4 * 64 - 16, b, 64, bo), (a, 64, ao, b, 64, ao + 2 * 64 - 16)):
+        assert call(*args) == _lib.ERR_ALIAS
+    assert call(None, 0, None, None, 0, None) == _lib.OK  # nothing to do: no launch
