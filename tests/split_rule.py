@@ -1,8 +1,9 @@
-"""The library's rules for a short last wave of output tiles (as documented in
-include/lors.h), restated for the tests: on whole-tile shapes its tiles are
-cut over their tokens into thin tiles; on other shapes, with
-LORS_FLAG_SPLIT_LAST_WAVE, they are split over K -- which shapes split, into
-how many pieces, and which output tiles run in pieces."""
+"""The library's rules for which kernel an output tile runs in (as documented
+in include/lors.h), restated for the tests: forwards of few tokens have a
+kernel of their own; elsewhere a short last wave of 256 x 256 tiles is cut into
+thin tiles, or, on shapes without whole tiles and with LORS_FLAG_SPLIT_LAST_WAVE,
+over K -- which shapes split, into how many pieces, and which output tiles run
+in pieces."""
 
 
 def up256(n):
@@ -69,6 +70,34 @@ def fwd_whole_tiles(L, R, C):
 def dx_whole_tiles(L, R, C):
     """The same for dX: tiles over L x C, K-steps over R."""
     return L % 256 == 0 and C % 256 == 0 and R % 64 == 0 and 256 * R * 2 < 2**31 and 64 * C * 2 < 2**31
+
+
+def thin_grid(L, N, cus=256):
+    """Tokens per thin tile of a grid that is one short wave: the least of
+    rounds x cost of a K-step, the larger tile on a tie."""
+    cost = lambda tm: -(-(-(-L // tm) * -(-N // 128)) // cus) * (0.45 + 0.0042 * tm)  # noqa: E731
+    return min((256, 192, 128, 64), key=cost)
+
+
+def kernels(kind, L, R, C, r, cus=256):
+    """The kernels that a call without the split flag runs ("few", "whole", or
+    the tokens per thin tile), and whether they check every lane of a copy."""
+    if kind == "fwd" and few_tokens(L, R, C, cus):
+        return {"few"}, C % 64 != 0
+    N, K = (R, C) if kind == "fwd" else (C, R)
+    checked = K % 64 != 0 or 256 * K * 2 >= 2**31 or (kind == "dx" and 64 * C * 2 >= 2**31)
+    tiles = -(-L // 256) * -(-N // 256)
+    if r <= 64:
+        tail = tiles % cus
+        if tail == 0 or 2 * tail > cus:
+            return {"whole"}, checked
+        if tail == tiles:
+            return {thin_grid(L, N, cus)}, checked
+        return {"whole", 512 // thin_q(tiles, cus)}, checked
+    if 2 * tiles <= cus:  # above rank 64: feature halves only
+        return {thin_grid(L, N, cus)}, checked
+    rest = (2 * tiles % cus + 1) // 2
+    return ({256, 64 if 8 * rest <= cus else 128} if 0 < 4 * rest <= cus else {256}), checked
 
 
 def thin_q(tiles, cus=256):

@@ -14,6 +14,7 @@ torch = pytest.importorskip("torch")
 from oracle import lors as olors  # noqa: E402
 from paper_2501_08582_amd import ops, synth  # noqa: E402
 from gpu_helpers import TOL, dev_to_f64, to_dev, to_f64, unprune, worst_tile  # noqa: E402
+import split_rule  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -276,3 +277,59 @@ def test_columns_past_the_contraction_keep_nothing(R, L, fmt):
     X, W, B, A = (to_dev(synth.f32_to_bf16_bits(v), "bf16") for v in (f(L, C), f(R, C) * Mk, B, f(r, C)))
     Y = ops.forward(X, W, ops.mask_pack(torch.from_numpy(Mk).cuda(), fmt), B, A, 1.5, fmt)
     assert torch.all(Y[:, R - 1] == float("inf")) and torch.isfinite(Y[:, :R - 1]).all()
+
+
+# Every instance of the tile kernels of Y and dX: whole tiles and each thin one,
+# each kind of copy and merge, at a rank of each 16-wide rank block (5 and 100
+# also fill up an 8-rank chunk).  Sizes as (tokens, output features) with the
+# kernels they are meant to run (up to rank 64 and above), on whole tiles and
+# with edges; 320 or 328 features are contracted (5 K-steps, or 6 of which the
+# last one holds 8 and checks its lanes).
+TILE_SIZES = {
+    "64": ((1024, 2048), (1000, 2040), {64}, {64}),
+    "128": ((1024, 4096), (520, 4168), {128}, {128}),
+    "192": ((1536, 4096), (1531, 4088), {192}, {192}),
+    "256": ((2048, 4096), (2040, 4088), {256}, {256}),
+    "whole": ((2304, 4096), (2060, 4168), {"whole"}, {256, 64}),
+}
+
+
+@pytest.mark.parametrize("copies", ["folded", "unfolded", "edges", "checked"])
+@pytest.mark.parametrize("tile", list(TILE_SIZES))
+@pytest.mark.parametrize("kind", ["fwd", "dx"])
+def test_tile_kernels(kind, tile, copies):
+    whole, edges, low, high = TILE_SIZES[tile]
+    L, N = whole if copies in ("folded", "unfolded") else edges
+    K, s = (328 if copies == "checked" else 320), (0.3 if copies == "unfolded" else 2.0)
+    R, C = (N, K) if kind == "fwd" else (K, N)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    mask = "2:4" if copies in ("unfolded", "checked") else "magnitude"
+    name = "llama2_7b_up_proj_2_4" if mask == "2:4" else "llama2_7b_q_proj"
+    inp = synth.make(synth.workload(name).with_(R=R, C=C, r=128, scale=s, seed=9000 + L + K), L=L)
+    inp.W = unprune(inp.W, inp.M, "bf16", seed=N)
+    bias = synth.f32_to_bf16_bits(np.random.default_rng(L).standard_normal(R).astype(np.float32) * 0.1)
+    X, W, bt, dY = (to_dev(t, "bf16") for t in (inp.X, inp.W, bias, inp.dY))
+    M = ops.mask_pack(torch.from_numpy(inp.M).cuda(), FMT[mask])
+    x, w, bb, dy = (to_f64(t, "bf16") for t in (inp.X, inp.W, bias, inp.dY))
+    for r in (5, 24, 48, 64, 72, 96, 100, 128):
+        print("tile kernels", kind, (R, C, L, r), tile, copies, flush=True)
+        if cus == 256:
+            assert split_rule.kernels(kind, L, R, C, r) == (low if r <= 64 else high, copies == "checked")
+        assert (split_rule.fwd_whole_tiles if kind == "fwd" else split_rule.dx_whole_tiles)(L, R, C) == (
+            copies in ("folded", "unfolded"))
+        Bh, Ah = np.ascontiguousarray(inp.B[:, :r]), inp.A[:r]
+        B, A = to_dev(Bh, "bf16"), to_dev(Ah, "bf16")
+        buf, out = _guarded((L, N), torch.bfloat16)
+        if kind == "fwd":
+            ops.forward(X, W, M, B, A, s, FMT[mask], bias=bt, out=out)
+        else:
+            dB, dA = (torch.empty(shape, device="cuda") for shape in ((R, r), (r, C)))
+            ops.backward(dY, X, W, M, B, A, s, FMT[mask], out=(out, dB, dA, None))
+        torch.cuda.synchronize()
+        assert torch.all(buf[:GUARD] == 0xA5) and torch.all(buf[GUARD + 2 * L * N:] == 0xA5), "a guard byte changed"
+        Wm = olors.merged_weight(w, inp.M, to_f64(Bh, "bf16"), to_f64(Ah, "bf16"), s)
+        want = x @ Wm.T + bb if kind == "fwd" else dy @ Wm
+        got = dev_to_f64(out)
+        assert np.all(np.isfinite(got)), f"rank {r}: not finite"
+        err, at = worst_tile(got, want, (64, 64))
+        assert err <= TOL["bf16"], f"rank {r}, block {at}: rel err {err:.3e}"
