@@ -42,6 +42,10 @@
  * values: exact unless they leave bf16's range.  Every other call applies s to
  * the fp32 product.
  * The fp32 dtype keeps every intermediate in fp32 (a debug/reference path).
+ * A call repeated on the same inputs gives the same bits of Y and dX.  The plan of
+ * a call depends on its shape, and with it the order of its fp32 sums: the last
+ * bits of a token's Y differ between a call of few tokens and a longer one, and
+ * between calls with and without LORS_FLAG_SPLIT_LAST_WAVE.
  *
  * Ownership: the caller owns every buffer.  The library never allocates
  * device memory; its scratch needs are reported by lors_workspace_bytes.
@@ -161,7 +165,8 @@ typedef enum lors_mask_format {
  *   byte count (products L*C, L*R, R*C times 4) at most 2^60; otherwise
  *   LORS_ERR_SHAPE.
  *   bf16: R % 8 == 0 and C % 8 == 0;  fp32: R % 4 == 0 and C % 4 == 0
- *   (16-byte rows); otherwise LORS_ERR_UNSUPPORTED.
+ *   (16-byte rows); fp32 also L and R at most 64 * 65535; otherwise
+ *   LORS_ERR_UNSUPPORTED.
  */
 typedef struct lors_problem {
     int64_t R;

@@ -81,7 +81,8 @@ lors_status_t check_problem(const lors_problem_t* p) {
     const int64_t row_align = p->dtype == LORS_DTYPE_BF16 ? 8 : 4;
     if (p->R % row_align != 0 || p->C % row_align != 0) return LORS_ERR_UNSUPPORTED;
     if (p->dtype == LORS_DTYPE_F32) {
-        // The fp32 kernels put token tiles of 64 on the second grid axis.
+        // The range of the fp32 (debug) path.  Its kernels cut larger grids into
+        // several launches and do not need the bound; callers may rely on it.
         if ((p->L + 63) / 64 > 65535 || (p->R + 63) / 64 > 65535) return LORS_ERR_UNSUPPORTED;
     }
     // Tile counts of the bf16 kernels must fit a 32-bit grid.

@@ -168,7 +168,8 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
     const uint8_t* zsrc = (const uint8_t*)g_zero_page + 16 * lane;
     // B-slab copy q of this wave lands at slab byte 1024*(4q + wave) + 16*lane,
     // i.e. row brow[q], physical chunk p; it carries logical chunk
-    // bswz(brow, p) -- ranks 8*that .. +7 of B row k0 + brow[q] zeros for ranks at or past r
+    // bswz(brow, p) -- ranks 8*that .. +7 of B row k0 + brow[q], zeros for
+    // ranks at or past r
     int brow[Lay::NB], bcol[Lay::NB];
     bool bval[Lay::NB];
 #pragma unroll
@@ -183,7 +184,6 @@ __global__ __launch_bounds__(NT, 1) void dx_kernel(
 
     // M^T is a plain bitmap whatever the caller's layout.
     if (tid < 16) *(u32x2*)(smem + Lay::LUT + 8 * tid) = select_lut16_entry<false>((uint32_t)tid);
-
 
     // ---- slab copies.  Copies 0..ND-1: dY slab rows 8*(ND*wave + q) + lane/8
     // (64 k per row); copies ND..ND+NWC-1: this wave's W block, its 32 NF

@@ -623,8 +623,8 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && tp.tm > 0) e = launch_fwd_thin_bf16(a, st, tp.n_full, tp.tail, tp.tm);
     if (e == hipSuccess && sp.split > 1)
-        e = launch_split_reduce_bf16(part, sp.n_full, sp.split, tiles_m, tiles_n, fwd_group_rows(tiles_m, tiles_n), a.L, (int)a.R, a.bias,
-                                     a.Y, st);
+        e = launch_split_reduce_bf16(part, sp.n_full, sp.split, tiles_m, tiles_n, fwd_group_rows(tiles_m, tiles_n), a.L,
+                                     (int)a.R, a.bias, a.Y, st);
     return e;
 }
 

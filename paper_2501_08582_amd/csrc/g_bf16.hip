@@ -101,8 +101,8 @@ __global__ __launch_bounds__(NT, 1) void g_kernel(
 
     // ---- asynchronous slab copies: copy pair q of this wave fills tile row
     // 2*(8*wave + q) + h of the dY slab and of the X slab; lane l covers
-    // physical chunk l % 32 of its row.  Rows past L and columns past R / C
-    // read the zero page.
+    // physical chunk l % 32 of its row.  Columns past R / C repeat the last chunk
+    // that exists (kChecked: they, and rows past L, read the zero page).
     const int pchunk = lane & 31;
     const uint8_t* zsrc = (const uint8_t*)g_zero_page + 16 * lane;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));

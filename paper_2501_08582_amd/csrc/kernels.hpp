@@ -64,8 +64,9 @@ inline int64_t split_part_bytes(const TailSplit& t) {
 // of the CUs, like tail_split.  A grid that is one such wave (no whole wave
 // before it) takes its token count from a cost of a K-step, 192 among them:
 // 0.45 + 0.0042 tm us were measured (5120 x 5120 and 4096 x 14336, rank 64:
-// 0.72 us at 64 tokens, 1.02 at 128, 1.5 at 256), times the rounds that
-// ceil(L/tm) ceil(N/128) thin tiles take on the CUs.
+// 0.72 us at 64 tokens, 1.02 at 128, 1.5 at 256; other ranks, whose merges cost
+// less or more, take the same line), times the rounds that ceil(L/tm)
+// ceil(N/128) thin tiles take on the CUs.
 // n_full: the tiles that run whole (the first n_full in the kernels' order);
 // for tm = 192 n_full = 0 and the logical tiles are 192 x 256.
 struct ThinPlan {

@@ -29,23 +29,23 @@ def _guarded(shape, dtype):
     return buf, buf[GUARD:GUARD + n].view(dtype).view(shape)
 
 
-# R, C multiples of 64: fixed copies in both directions; R or C % 64 = 8: the
-# last K-step of dX or the forward checks its lanes
+# R a multiple of 64: fixed copies in dX; R % 64 = 8: its last K-step checks its
+# lanes.  The forward has few tokens but where noted.
 @pytest.mark.parametrize("R,C,L,r,mask,scale", [
     (64, 64, 1, 16, "magnitude", 2.0),        # one token, one K-step, a quarter of a tile
     (320, 192, 63, 5, "2:4", 2.0),            # below one token K-step of the weight gradient
     (192, 448, 65, 16, "magnitude", 0.3),     # two token K-steps, 63 rows shared
     (448, 576, 129, 40, "2:4", 0.5),
     (264, 192, 200, 8, "magnitude", 2.0),     # dX: checked copies, thin
-    (192, 264, 321, 64, "magnitude", 1.5),    # forward: checked copies, thin
-    (1032, 1096, 130, 24, "2:4", 2.0),        # both, odd feature halves
-    (4160, 4224, 513, 16, "magnitude", 2.0),  # three token tiles, the last of one token
-    (256, 256, 300, 100, "magnitude", 2.0),   # ranks above 64: feature halves, no whole wave
+    (192, 264, 321, 64, "magnitude", 1.5),
+    (1032, 1096, 130, 24, "2:4", 2.0),        # the same, odd feature halves
+    (4160, 4224, 513, 16, "magnitude", 2.0),  # forward and dX: 128-token thin tiles, the last of one token
+    (256, 256, 300, 100, "magnitude", 2.0),   # ranks above 64
     (264, 328, 193, 72, "2:4", 0.3),
     (4096, 192, 1100, 24, "magnitude", 2.0),  # forward: a grid of 192-token thin tiles
     (192, 4160, 1090, 24, "2:4", 1.5),        # dX: the same
     (200, 4096, 1100, 128, "2:4", 2.0),       # dX: the same above rank 64, checked copies
-    (320, 4160, 2300, 128, "magnitude", 1.0), # dX: a wave of feature halves, then thinner tiles
+    (320, 4160, 2300, 128, "magnitude", 1.0), # dX: a wave of feature halves, then thinner tiles; forward: thin
 ])
 def test_edges(R, C, L, r, mask, scale):
     name = "llama2_7b_up_proj_2_4" if mask == "2:4" else "llama2_7b_q_proj"

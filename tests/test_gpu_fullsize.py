@@ -52,7 +52,7 @@ def test_full_size_sampled(name):
 @pytest.mark.parametrize("r", [4, 100])
 def test_full_size_padded_rank_sampled(r):
     """Ranks that are not a multiple of 8 (the backward pads B in the
-    workspace; 100 also splits into two rank passes) at the 4096 x 4096 size."""
+    workspace; 100 also runs as thin tiles only) at the 4096 x 4096 size."""
     _check_sampled(synth.workload("llama2_7b_q_proj").with_(r=r))
 
 

@@ -67,7 +67,7 @@ def _check(inp, label, **kw):
     (520, 776, 300, 16),    # ragged in every dimension
     (512, 512, 512, 64),    # whole tiles (fixed-offset copies)
     (264, 1032, 77, 5),     # odd rank: padded B in the backward
-    (512, 264, 260, 100),   # two rank passes (the second takes W as zero)
+    (512, 264, 260, 100),   # a rank above 64
 ])
 def test_unpruned_weight_with_non_finite_masked_entries(kind, R, C, L, r):
     inp = _inputs(kind, R=R, C=C, L=L, r=r, seed=4000 + R + r)

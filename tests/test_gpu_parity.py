@@ -422,7 +422,7 @@ def test_straight_through_equals_exact_for_a_dense_mask():
 
 # ---------------------------------------------------------------------------
 # seeded shapes at every rank-bucket edge of the kernels (16-wide rank blocks,
-# two passes above 64, padded B for ranks that are not a multiple of 8),
+# feature halves above 64, padded B for ranks that are not a multiple of 8),
 # ragged in R, C and L, both mask kinds
 # ---------------------------------------------------------------------------
 def _edge_cases():
@@ -447,22 +447,22 @@ def test_parity_rank_bucket_edges(R, C, L, r, mask):
 
 
 # ---------------------------------------------------------------------------
-# ranks above 64 that are multiples of 8 run as two passes of the 64-rank
-# kernels (the second with W taken as zero, added onto Y and dX)
+# ranks above 64: dX as thin tiles only, the forward in the kernel for few
+# tokens at these sizes (test_gpu_edges.py has its thin tiles)
 # ---------------------------------------------------------------------------
 @pytest.mark.parametrize("R,C,L,r,mask", [
-    (520, 776, 300, 96, "magnitude"),   # ragged, second pass r = 32
-    (264, 1032, 77, 72, "2:4"),         # second pass r = 8
-    (768, 512, 513, 128, "magnitude"),  # second pass r = 64, one token past a tile
-    (512, 768, 512, 80, "2:4"),         # whole tiles: the first pass as thin tiles, the second whole
+    (520, 776, 300, 96, "magnitude"),   # ragged
+    (264, 1032, 77, 72, "2:4"),
+    (768, 512, 513, 128, "magnitude"),  # one token past a tile
+    (512, 768, 512, 80, "2:4"),         # whole tiles
 ])
-def test_parity_two_pass_ranks(R, C, L, r, mask):
+def test_parity_ranks_above_64(R, C, L, r, mask):
     name = "llama2_7b_up_proj_2_4" if mask == "2:4" else "llama2_7b_q_proj"
     inp = _inputs(name, R=R, C=C, L=L, r=r, seed=R + 3 * C + L + r)
     _check_all(inp)
 
 
-def test_parity_two_pass_bias_and_straight_through():
+def test_parity_rank_112_bias_and_straight_through():
     inp = _inputs("llama2_7b_q_proj", R=264, C=520, L=130, r=112, seed=99)
     rng = np.random.default_rng(5)
     bias = synth.f32_to_bf16_bits(rng.standard_normal(264).astype(np.float32))
@@ -487,8 +487,8 @@ def test_parity_two_pass_bias_and_straight_through():
     (520, 776, 300, 4, "magnitude"),    # ragged
     (264, 1032, 77, 5, "2:4"),
     (512, 768, 512, 12, "magnitude"),   # whole tiles (fixed-offset copies)
-    (768, 512, 513, 100, "magnitude"),  # two passes: 64, then 36 of 40 padded
-    (512, 512, 256, 127, "2:4"),        # two passes, whole tiles, 63 of 64
+    (768, 512, 513, 100, "magnitude"),  # above 64, 100 of 104
+    (512, 512, 256, 127, "2:4"),        # above 64, whole tiles, 127 of 128
 ])
 def test_parity_padded_ranks(R, C, L, r, mask):
     name = "llama2_7b_up_proj_2_4" if mask == "2:4" else "llama2_7b_q_proj"
@@ -582,7 +582,7 @@ def test_weight_gradient_tail_split(R, C, L, r, mask):
 # ---------------------------------------------------------------------------
 # LORS_FLAG_SPLIT_LAST_WAVE: forward and dX tiles of a short last wave cut
 # over K, fp32 partials reduced in a fixed order, within a workspace budget
-# of R*C/4 bytes -- on shapes without whole tiles (whole-tile shapes cut such
+# of R*C/4 bytes -- on shapes without whole tiles (other calls cut such
 # waves into thin tiles instead, see test_gpu_thin.py).  Shapes whose grids
 # end in a short wave that the budget can split (tests/split_rule.py restates
 # the rule; test_abi checks the library against it):
@@ -705,7 +705,7 @@ def _guards_intact(buf, n):
 
 @pytest.mark.parametrize("R,C,L,r,mask,bias,split", [
     (520, 776, 300, 16, "magnitude", True, False),   # ragged in every dimension
-    (264, 520, 130, 112, "2:4", True, False),        # two rank passes (the second adds onto Y and dX)
+    (264, 520, 130, 112, "2:4", True, False),        # a rank above 64
     (264, 1032, 77, 5, "magnitude", False, True),    # padded B in the workspace; no split (small R*C)
     (1024, 65792, 200, 5, "magnitude", True, True),  # split dX with partials in the workspace, few-token forward
     (7400, 3016, 2280, 5, "magnitude", True, True),  # split forward with partials in the workspace
@@ -758,7 +758,7 @@ def test_outputs_and_workspace_stay_in_bounds(R, C, L, r, mask, bias, split):
 @pytest.mark.parametrize("r,mask", [(16, "magnitude"), (48, "2:4"), (64, "magnitude"), (32, "2:4")])
 def test_parity_scales_whole_tiles(scale, r, mask):
     name = "llama2_7b_up_proj_2_4" if mask == "2:4" else "llama2_7b_q_proj"
-    inp = _inputs(name, R=512, C=768, L=512, r=r, scale=scale, seed=3000 + r)
+    inp = _inputs(name, R=2048, C=256, L=512, r=r, scale=scale, seed=3000 + r)  # past the few-token forward
     _check_all(inp)
     if mask == "2:4" and r <= 64:
         _check_all(inp, sparse_mfma=True)

@@ -1,4 +1,5 @@
-"""Thin tiles of a short last wave (forward and dX, whole-tile shapes).
+"""Thin tiles of a short last wave after whole ones (forward and dX), on shapes of
+whole tiles; test_gpu_edges.py has grids of thin tiles only and shapes with edges.
 
 When a grid of 256 x 256 output tiles ends in a wave that fills at most half
 of the CUs, the library cuts each of its tiles into 2, 4 or 8 thin tiles (as
