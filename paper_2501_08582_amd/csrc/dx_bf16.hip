@@ -634,8 +634,10 @@ hipError_t launch_rk(const LayerArgs& a, hipStream_t st, int ra) {
     const bool krag = !dx_fixed_copies(a.R, a.C);
     const bool fold = folds(a);
     // A short last wave is cut over K when the caller gave room for the
-    // pieces' partial sums (shapes without whole tiles); otherwise it runs as thin tiles (the same bits as whole
-    // ones, no workspace).
+    // pieces' partial sums (shapes without whole tiles); otherwise it runs as
+    // thin tiles (the same bits as whole ones, no workspace).  Thin / split,
+    // backward at rank 64 (us): 65792 x 2048, 200 tokens (8 tiles in 8 pieces)
+    // 1100 / 545; 4096 x 11008, 1531 tokens (2 in 8) 406 / 378.
     TailSplit sp{tiles, 1, tiles};
     if (a.split_ws != nullptr && !dx_whole_tiles(a.L, a.R, a.C))
         sp = tail_split(tiles, (a.R + BK - 1) / BK, a.split_budget);
