@@ -82,10 +82,10 @@ __device__ __forceinline__ uint32_t merge_pair_all(uint32_t raw, float t0, float
 // rank-r product; see rank_mfma2), with the matrix-result -> VALU wait states.
 template <int RK>
 __device__ __forceinline__ void rank_mfma1(f32x16& T, const bf16x8 (&a)[RK], const bf16x8 (&b)[RK]) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(T) : "v"(a[0]), "v"(b[0]));
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(T) : "v"(a[0]), "v"(b[0]));
 #pragma unroll
     for (int c = 1; c < RK; ++c)
-        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+&v"(T) : "v"(a[c]), "v"(b[c]));
+        asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+&v"(T) : "v"(a[c]), "v"(b[c]));
     if constexpr (RK == 1)
         asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 2" : "+v"(T) : "v"(a[0]));
     else if constexpr (RK == 2)
@@ -257,11 +257,13 @@ __global__ __launch_bounds__(NT, 1) void fwd24_kernel(
     // kx, kw, ki: the operands of the previous structured-sparse MFMA.  The
     // matrix core reads its sources over several passes after issue, so they
     // are held here, as inputs of the next one, and no instruction in
-    // between may reuse their registers.
+    // between may reuse their registers.  (The leading wait states: see
+    // rank_mfma2.  Without them the first K-step of some instances read an
+    // accumulator or an operand that had just been moved as it was before.)
     auto smf = [&](int i, const bf16x16& xf, const u32x4 (&wf)[2], const uint32_t (&ix)[2], const bf16x16& kx,
                    const u32x4& kw, uint32_t ki) {
         const int mb = i >> 1, nb = i & 1;
-        asm volatile("v_smfmac_f32_32x32x32_bf16 %0, %1, %2, %3\n\ts_nop 7"
+        asm volatile("s_nop 1\n\tv_smfmac_f32_32x32x32_bf16 %0, %1, %2, %3\n\ts_nop 7"
                      : "+a"(acc[nb][mb])
                      : "v"(wf[nb]), "v"(xf), "v"(ix[nb]), "v"(kx), "v"(kw), "v"(ki));
     };

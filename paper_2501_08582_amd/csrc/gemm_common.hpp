@@ -209,17 +209,20 @@ __device__ __forceinline__ void rank_wait(f32x16 (&T)[NB], const bf16x8 (&a)[RK]
 // or one for a tile of half the features), with T in VGPRs.
 // The main accumulators fill the accumulation registers, so results that the
 // VALU consumes are produced by inline-assembly MFMAs writing VGPRs directly
-// (chained accumulation into the same registers needs no wait states).  The
+// (chained accumulation into the same registers needs no wait states).  An
+// operand register that a VALU instruction wrote needs two wait states before
+// the MFMA reads it; the compiler, which may move an operand right in front of
+// the assembly, does not know of them, so each MFMA brings its own.  The
 // final s_nop block covers the matrix-result -> VALU-read latency; it also
 // keeps the A fragments allocated until the matrix core has consumed them.
 template <int RK, int NB>
 __device__ __forceinline__ void rank_mfma2(f32x16 (&T)[NB], const bf16x8 (&a)[RK], const bf16x8 (&b)[NB][RK]) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(T[nb]) : "v"(a[0]), "v"(b[nb][0]));
+        asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(T[nb]) : "v"(a[0]), "v"(b[nb][0]));
 #pragma unroll
         for (int c = 1; c < RK; ++c)
-            asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+&v"(T[nb]) : "v"(a[c]), "v"(b[nb][c]));
+            asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+&v"(T[nb]) : "v"(a[c]), "v"(b[nb][c]));
     }
     rank_wait<RK, NB>(T, a);
 }
@@ -236,7 +239,7 @@ __device__ __forceinline__ void rank_mfma2_acc(f32x16 (&T)[NB], const bf16x8 (&a
         asm volatile("s_nop 4\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+&v"(T[nb]) : "v"(a[0]), "v"(b[nb][0]));
 #pragma unroll
         for (int c = 1; c < RK; ++c)
-            asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+&v"(T[nb]) : "v"(a[c]), "v"(b[nb][c]));
+            asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+&v"(T[nb]) : "v"(a[c]), "v"(b[nb][c]));
     }
     rank_wait<RK, NB>(T, a);
 }

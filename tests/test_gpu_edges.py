@@ -333,3 +333,21 @@ def test_tile_kernels(kind, tile, copies):
         assert np.all(np.isfinite(got)), f"rank {r}: not finite"
         err, at = worst_tile(got, want, (64, 64))
         assert err <= TOL["bf16"], f"rank {r}, block {at}: rel err {err:.3e}"
+
+
+@pytest.mark.parametrize("R,C,L,r", [(256, 64, 768, 1), (264, 64, 200, 5), (512, 128, 256, 24), (72, 40, 33, 64), (256, 64, 256, 16)])
+def test_sparse_mfma_first_k_steps(R, C, L, r):
+    """The structured-sparse forward with one or two K-steps, where the first
+    operands and accumulators are a large part of the result: the same bits on
+    every call, whatever ran before, and the oracle's values."""
+    inp = synth.make(synth.workload("llama2_7b_up_proj_2_4").with_(R=R, C=C, r=r, seed=6100 + R + r), L=L)
+    inp.W = unprune(inp.W, inp.M, "bf16", seed=r)
+    X, W, B, A = (to_dev(t, "bf16") for t in (inp.X, inp.W, inp.B, inp.A))
+    M = ops.mask_pack(torch.from_numpy(inp.M).cuda(), ops.TWO_FOUR)
+    first = ops.forward(X, W, M, B, A, 2.0, ops.TWO_FOUR, sparse_mfma=True)
+    x, w, b, a = (to_f64(t, "bf16") for t in (inp.X, inp.W, inp.B, inp.A))
+    err, at = worst_tile(dev_to_f64(first), olors.forward(x, w, inp.M, b, a, 2.0), (32, 32))
+    assert err <= TOL["bf16"], f"block {at}: rel err {err:.3e}"
+    for _ in range(8):
+        ops.backward(first, X, W, M, B, A, 2.0, ops.TWO_FOUR)
+        assert torch.equal(ops.forward(X, W, M, B, A, 2.0, ops.TWO_FOUR, sparse_mfma=True), first)
