@@ -1,11 +1,12 @@
 """The built device code keeps the wait states that inline assembly hides.
 
 A matrix instruction (MFMA, structured-sparse MFMA) may read a register only two
-wait states after a vector-ALU instruction wrote it.  The compiler sees to that
-for its own matrix instructions, not for those in inline assembly, in front of
-which it is free to place the move of an operand.  This test reads the listing
-of the library's gfx950 code objects (built here from these sources) and looks
-at every matrix instruction, across branches.  CPU only.
+wait states after a vector-ALU instruction wrote it, and a vector memory
+instruction a scalar register (its base address) only five after.  The compiler
+sees to that for its own instructions, not for those in inline assembly, in
+front of which it is free to place the move of an operand.  This test reads the
+listing of the library's gfx950 code objects (built here from these sources) and
+looks at every such instruction, across branches.  CPU only.
 """
 import os
 import re
@@ -17,14 +18,14 @@ import pytest
 from paper_2501_08582_amd import _lib
 
 OBJDUMP = shutil.which("llvm-objdump") or "/opt/rocm/llvm/bin/llvm-objdump"
-NEED = 2
+MATRIX_WAIT, BASE_WAIT = 2, 5
 MATRIX = ("v_mfma", "v_smfmac")
-NO_VGPR = ("v_cmp", "v_readfirstlane", "v_readlane", "v_nop")
+MEMORY = ("global_", "buffer_", "flat_", "scratch_")
 
 
 def _regs(text):
     out = set()
-    for m in re.finditer(r"\b([va])\[(\d+):(\d+)\]|\b([va])(\d+)\b", text):
+    for m in re.finditer(r"\b([vas])\[(\d+):(\d+)\]|\b([vas])(\d+)\b", text):
         if m.group(1):
             out |= {m.group(1) + str(i) for i in range(int(m.group(2)), int(m.group(3)) + 1)}
         else:
@@ -51,11 +52,13 @@ def _functions(listing):
 
 
 def _written(mn, ops):
-    """Vector registers that a vector-ALU instruction writes."""
-    if not mn.startswith("v_") or mn.startswith(MATRIX + NO_VGPR):
+    """Registers that a vector-ALU instruction writes (its first operand; the second one too of a swap or
+    where it takes a carry or a mask)."""
+    if not mn.startswith("v_") or mn.startswith(MATRIX + ("v_nop",)):
         return set()
     o = _operands(ops)
-    return _regs(o[0]) | (_regs(o[1]) if mn.startswith("v_swap") else set())
+    two = mn.startswith(("v_swap", "v_mad_u64", "v_mad_i64", "v_div_scale")) or "_co_" in mn
+    return set().union(*(_regs(x) for x in o[:2 if two else 1]))
 
 
 def _violations(code):
@@ -66,22 +69,26 @@ def _violations(code):
         if target and mn.startswith(("s_branch", "s_cbranch")):
             jumps.setdefault(at.get(int(target, 16)), []).append(i)
 
-    def back(i, left, want, of):
+    def back(i, need, left, want, of):
         before = [] if i == 0 or code[i - 1][0] in ("s_branch", "s_endpgm") else [i - 1]
         for p in before + jumps.get(i, []):
             mn, ops = code[p][:2]
             if _written(mn, ops) & want:
-                bad.append(f"{mn} {ops} -> {code[of][0]} {code[of][1]}: {NEED - left} wait states")
+                bad.append(f"{mn} {ops} -> {code[of][0]} {code[of][1]}: {need - left} wait states")
                 continue
             states = int(ops, 0) + 1 if mn == "s_nop" else 1
             if states < left:
-                back(p, left - states, want, of)
+                back(p, need, left - states, want, of)
 
     for i, (mn, ops, _, _) in enumerate(code):
+        o = _operands(ops)
         if mn.startswith(MATRIX):
-            o = _operands(ops)
             read = o if mn.startswith("v_smfmac") else o[1:]  # smfmac accumulates into its first operand
-            back(i, NEED, set().union(*(_regs(x) for x in read)), i)
+            back(i, MATRIX_WAIT, MATRIX_WAIT, set().union(*(_regs(x) for x in read)), i)
+        elif mn.startswith(MEMORY):
+            base = {r for r in _regs(ops) if r[0] == "s"}
+            if base:
+                back(i, BASE_WAIT, BASE_WAIT, base, i)
     return bad
 
 
@@ -103,9 +110,13 @@ def test_the_reader_sees_a_missing_wait():
     assert not bad("v_mov_b32_e32 v2, v19", mfma) and not bad("ds_read_b64 v[94:95], v2", mfma)
     # over a branch: the move at the end of a loop, the product at its head
     assert bad("s_nop 7", mfma, "v_mov_b32_e32 v94, v19", "s_cbranch_scc1 65532@0x4")
+    load = "global_load_lds_dwordx4 v131, s[16:17]"
+    assert bad("v_readfirstlane_b32 s16, v1", "s_mov_b32 m0, s36", "s_nop 0", load)
+    assert not bad("v_readfirstlane_b32 s16, v1", "s_nop 4", load)
+    assert not bad("s_mov_b32 s16, s2", load) and not bad("v_readfirstlane_b32 s18, v1", load)
 
 
-def test_matrix_instructions_wait_for_their_operands(tmp_path):
+def test_instructions_wait_for_their_operands(tmp_path):
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
     if not os.path.exists(_lib.LIB_PATH):
@@ -121,4 +132,4 @@ def test_matrix_instructions_wait_for_their_operands(tmp_path):
             seen += sum(mn.startswith(MATRIX) for mn, *_ in code)
             bad += [f"{fn}: {b}" for b in _violations(code)]
     assert seen > 5000, "the library's matrix instructions were not found"
-    assert not bad, f"{len(bad)} matrix instructions read an operand too early:\n" + "\n".join(bad[:10])
+    assert not bad, f"{len(bad)} instructions read an operand too early:\n" + "\n".join(bad[:10])
