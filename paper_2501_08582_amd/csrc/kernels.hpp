@@ -90,7 +90,9 @@ int device_cus();
 // few (us): 4096 x 4096, rank 16, 1 / 64 / 128 tokens 42 / 42 / 43 against 13 /
 // 25 / 30, 256 tokens 43 against 45; 14336 x 4096, 32 / 64 tokens 53 / 55
 // against 44 / 62; 4096 x 14336, rank 64, 64 / 128 tokens 172 / 170 against
-// 104 / 123.  (The bound on C keeps its 32-bit offsets of 128 rows.)
+// 104 / 123.  The line is the same at every rank (128, thin against few: 4096 x
+// 4096, 1 / 128 tokens 67 / 68 against 30 / 39, 1024 x 4096, 512 tokens 69 against
+// 40).  (The bound on C keeps its 32-bit offsets of 128 rows.)
 bool fwd_few_tokens(int64_t L, int64_t R, int64_t C);
 // Shapes of whole tiles, which never split over K: 256 x 256 tiles and 64-wide
 // K-steps cover the forward's L x R, K = C (dX's L x C, K = R) exactly.
